@@ -198,3 +198,37 @@ def test_attn_stats_workload(name):
     announce(f"attn stats {name}")
     a = synth.stats_inputs(name, seed=0)
     _stats_case(a, a["r0"], a["masked"].numpy(), a["drafted"].numpy())
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Lr,d", [
+    (1, 4, 2, 31, 128), (1, 32, 8, 300, 64),   # one tile per workgroup: eight waves share it
+    (1, 128, 8, 128, 64),                      # two tiles: four waves each
+    (2, 64, 8, 190, 128),                      # three: two waves each
+    (1, 256, 8, 33, 128),                      # two tiles, the second of one position
+    (2, 128, 8, 250, 64),                      # eight: one wave each
+    (2, 128, 8, 289, 64), (2, 128, 8, 600, 64)])  # ten and nineteen: two tiles per wave
+def test_attn_stats_lists(B, Hq, Hkv, Lr, d):
+    """The lists of masked queries and drafted keys, at every division of a workgroup's waves:
+    all or none of the positions masked or drafted, single ones, counts at the edges of a
+    32-row tile, and seeds that are themselves masked and drafted (their diagonal is live)."""
+    announce(f"attn stats lists B{B} Hq{Hq} Lr {Lr} d{d}")
+    L, r0 = Lr + 45, 24
+    a = synth.attn_inputs("tiny", seed=Lr + Hq, max_seeds=24, B=B, Hq=Hq, Hkv=Hkv, L=L, d=d,
+                          dtype="bf16", prompt=0, unmasked_gen=L, n_seeds=24)
+    seeds = a["seed_idx"].numpy() - r0
+    for case in range(4):
+        masked, drafted = np.zeros((B, Lr), np.uint8), np.zeros((B, Lr), np.uint8)
+        if case == 0:
+            masked[:] = 1
+            drafted[:, Lr - 1] = 1
+        elif case == 1:
+            drafted[:] = 255  # nonzero is a member
+        elif case == 2:
+            masked[:, : min(32, Lr)] = 1
+            drafted[:, Lr - min(33, Lr):] = 1
+            for b in range(B):
+                inside = seeds[b][(seeds[b] >= 0) & (seeds[b] < Lr)]
+                masked[b, inside] = drafted[b, inside] = 1
+        else:
+            masked[:, 0] = 1
+        _stats_case(a, r0, masked, drafted)
