@@ -641,8 +641,22 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_bf16_kernel(const Para
 }
 
 // ----------------------------------------------------------------------------------------
-// fp32 path: one wave per 64 queries of one (b, h); each lane owns one query row and walks
-// the keys with an exact online softmax.  Same override / leave-one-out rule as above.
+// fp32 path.  Same override / leave-one-out rule as above, on the fp32 matrix instruction
+// (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).  One workgroup of up to 8 waves
+// per 16 query rows of one (b, h); the waves take the 16-key tiles in turn and merge their
+// (max, sum, O) through LDS.  The calls are small (a layer of tens to hundreds of tokens), so
+// what bounds them is latency: 16-row tiles give the most workgroups and the shortest chain per
+// tile (1024 matrix cycles at d = 64), each wave requests its next tile before it works on one,
+// and every operand is read from memory in the layout the instruction wants, without LDS:
+//   S^T = K Q^T   lane (i, g) = (lane % 16, lane / 16) holds 4 consecutive d of key row i (of
+//                 query row i), d = 16 s + 4 g + e; product (s, e) takes element e of both, so
+//                 the order of d is the same on both sides
+//   O^T = V^T P^T the S^T registers of lane (i, g) are keys 4 g + r of query i: the B operand
+//                 of product r.  A: 4 consecutive d of key row 4 g + r, d = 64 c + 4 i + e;
+//                 accumulator (c, e) then holds O at d = 64 c + 4 row + e
+// Measured against one lane per query row walking the keys: B1 H2 L64 d64 51.2 -> 4.9 us,
+// B2 H8 L640 d64 464 -> 40, B1 H32 L1024 d128 2040 -> 251 (69 of the instruction's 157 TFLOP/s;
+// placing a head's workgroups on one XCD changed nothing, so it is not L2 misses that bound it).
 // ----------------------------------------------------------------------------------------
 struct ParamsF {
   const float* q;
@@ -656,104 +670,175 @@ struct ParamsF {
   float* lse;
   int B, Hq, Hkv, L, max_seeds, group, n_qt;
   float c2;
+  int64_t n_wg;  // query tiles in all
   int64_t q_sb, q_sh, q_sl, kv_sb, kv_sh, kv_sl;
 };
 
+constexpr int kFWaves = 8;  // most waves per workgroup
+constexpr int kFT = 16;     // queries per workgroup, keys per tile
+
 template <int D>
-__global__ __launch_bounds__(64, 1) void cover_attn_f32_kernel(const ParamsF p) {
-  constexpr int TK = 32;  // keys per LDS tile
-  __shared__ __attribute__((aligned(16))) float ks[TK][D];
-  __shared__ __attribute__((aligned(16))) float vs[TK][D];
+__global__ __launch_bounds__(64 * kFWaves) void cover_attn_f32_kernel(const ParamsF p) {
+  constexpr int KS = D / 16, DC = D / 64;
+  __shared__ __attribute__((aligned(16))) float sO[kFWaves][kFT][D + 4];
+  __shared__ float sM[kFWaves][kFT], sL[kFWaves][kFT];
   __shared__ uint32_t bits[COVER_MAX_L / 32];
-  const int lane = threadIdx.x;
-  const int qt = blockIdx.x % p.n_qt;
-  const int bh = blockIdx.x / p.n_qt;
-  const int h = bh % p.Hq, b = bh / p.Hq;
-  const int g = h / p.group;
+  const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, nw = nth >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, g4 = lane >> 4;
   const int L = p.L;
-  const int64_t kvoff = b * p.kv_sb + g * p.kv_sh;
+  const int n_kt = (L + kFT - 1) / kFT;
 
-  const int nwords = (L + 31) >> 5;
-  for (int w = lane; w < nwords; w += 64) bits[w] = 0u;
-  __syncthreads();
-  int ns = 0;
-  if (p.max_seeds > 0) {
-    ns = p.n_seed[b];
-    ns = ns < 0 ? 0 : (ns > p.max_seeds ? p.max_seeds : ns);
-  }
-  for (int t = lane; t < ns; t += 64) {
-    const int j = p.seed_idx[(int64_t)b * p.max_seeds + t];
-    if ((unsigned)j < (unsigned)L) atomicOr(&bits[j >> 5], 1u << (j & 31));
-  }
-  __syncthreads();
+  for (int64_t li = blockIdx.x; li < p.n_wg; li += gridDim.x) {
+    const int qt = (int)(li % p.n_qt);
+    const int64_t bh = li / p.n_qt;
+    const int h = (int)(bh % p.Hq), b = (int)(bh / p.Hq);
+    const int g = h / p.group;
+    const int64_t kvoff = b * p.kv_sb + g * p.kv_sh;
+    const float* qbase = p.q + b * p.q_sb + h * p.q_sh;
 
-  const int qi = qt * 64 + lane;
-  const int qc = min(qi, L - 1);
-  const float* qrow = p.q + b * p.q_sb + h * p.q_sh + (int64_t)qc * p.q_sl;
-  float qv[D];
+    const int ns_raw = p.max_seeds > 0 ? p.n_seed[b] : 0;
+    const int j_first = tid < p.max_seeds ? p.seed_idx[(int64_t)b * p.max_seeds + tid] : -1;
+    const int qi = qt * kFT + i16;
+    f32x4 qf[KS];
 #pragma unroll
-  for (int k = 0; k < D; k += 4) *(f32x4*)(qv + k) = *(const f32x4*)(qrow + k);
-  const bool seed = qi < L && ((bits[qc >> 5] >> (qc & 31)) & 1u);
-  float s_live = 0.0f;
-  if (seed) {
-    const float* kr = p.kl + kvoff + (int64_t)qc * p.kv_sl;
-    for (int k = 0; k < D; ++k) s_live = __builtin_fmaf(qv[k], kr[k], s_live);
-  }
-  float m = kInitMax, l = 0.0f;
-  float o[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) o[k] = 0.0f;
-
-  for (int k0 = 0; k0 < L; k0 += TK) {
+    for (int s = 0; s < KS; ++s)
+      qf[s] = *(const f32x4*)(qbase + (int64_t)min(qi, L - 1) * p.q_sl + 16 * s + 4 * g4);
+    for (int w = tid; w < (L + 31) >> 5; w += nth) bits[w] = 0u;
     __syncthreads();
-    for (int idx = lane; idx < TK * D / 4; idx += 64) {
-      const int row = idx / (D / 4), c = idx % (D / 4);
-      const int key = min(k0 + row, L - 1);
-      const bool sd = (bits[key >> 5] >> (key & 31)) & 1u;
-      const int64_t off = kvoff + (int64_t)key * p.kv_sl + c * 4;
-      *(f32x4*)(&ks[row][c * 4]) = *(const f32x4*)((sd ? p.kc : p.kl) + off);
-      *(f32x4*)(&vs[row][c * 4]) = *(const f32x4*)((sd ? p.vc : p.vl) + off);
+    const int ns = ns_raw < 0 ? 0 : (ns_raw > p.max_seeds ? p.max_seeds : ns_raw);
+    if (tid < ns && (unsigned)j_first < (unsigned)L) atomicOr(&bits[j_first >> 5], 1u << (j_first & 31));
+    for (int t = tid + nth; t < ns; t += nth) {
+      const int j = p.seed_idx[(int64_t)b * p.max_seeds + t];
+      if ((unsigned)j < (unsigned)L) atomicOr(&bits[j >> 5], 1u << (j & 31));
     }
     __syncthreads();
-    const int kn = min(TK, L - k0);
-    for (int j = 0; j < kn; ++j) {
-      const int key = k0 + j;
-      const bool diag = seed && key == qi;
-      float s = 0.0f;
-      if (diag) {
-        s = s_live;
-      } else {
+    auto is_seed = [&](int j) -> bool { return (bits[j >> 5] >> (j & 31)) & 1u; };
+    const bool row_seed = qi < L && is_seed(qi);
+
+    // one tile's operands: rows past L repeat the last (their scores are masked)
+    auto load = [&](int kt, f32x4* kf, f32x4 (*vf)[DC]) __attribute__((always_inline)) {
+      const int key = min(kt * kFT + i16, L - 1);
+      const float* kr = (is_seed(key) ? p.kc : p.kl) + kvoff + (int64_t)key * p.kv_sl + 4 * g4;
 #pragma unroll
-        for (int k = 0; k < D; ++k) s = __builtin_fmaf(qv[k], ks[j][k], s);
-      }
-      const float t = s * p.c2;
-      if (t > m) {
-        const float alpha = __builtin_amdgcn_exp2f(m - t);
-        l *= alpha;
+      for (int s = 0; s < KS; ++s) kf[s] = *(const f32x4*)(kr + 16 * s);
 #pragma unroll
-        for (int k = 0; k < D; ++k) o[k] *= alpha;
-        m = t;
-      }
-      const float pw = __builtin_amdgcn_exp2f(t - m);
-      l += pw;
-      if (diag) {
-        const float* vr = p.vl + kvoff + (int64_t)qi * p.kv_sl;
-        for (int k = 0; k < D; ++k) o[k] = __builtin_fmaf(pw, vr[k], o[k]);
-      } else {
+      for (int r = 0; r < 4; ++r) {
+        const int kv = min(kt * kFT + 4 * g4 + r, L - 1);
+        const float* vr = (is_seed(kv) ? p.vc : p.vl) + kvoff + (int64_t)kv * p.kv_sl + 4 * i16;
 #pragma unroll
-        for (int k = 0; k < D; ++k) o[k] = __builtin_fmaf(pw, vs[j][k], o[k]);
+        for (int c = 0; c < DC; ++c) vf[r][c] = *(const f32x4*)(vr + 64 * c);
       }
+    };
+    // max / sum over the four lanes that share a query
+    auto quad_max = [](float x) {
+      const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      x = fmax2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+      return swap_max(x);
+    };
+    auto quad_sum = [](float x) {
+      const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      return swap_add(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+    };
+    float m = kInitMax, l = 0.0f;
+    f32x4 o[DC][4];
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[c][e] = (f32x4){};
+    f32x4 kf[KS], kn[KS], vf[4][DC], vn[4][DC];
+    if (wave < n_kt) load(wave, kf, vf);
+    for (int kt = wave; kt < n_kt; kt += nw) {
+      if (kt + nw < n_kt) load(kt + nw, kn, vn);
+      f32x4 s0 = {}, s1 = {};
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s][e], qf[s][e], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[s][e + 1], qf[s][e + 1], s1, 0, 0, 0);
+        }
+      float t[4], mx = kInitMax;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int key = kt * kFT + 4 * g4 + r;
+        t[r] = (s0[r] + s1[r]) * p.c2;
+        // keys past L and a seed row's own (cached) column get no weight; its live diagonal
+        // term joins in the merge
+        if (key >= L || (row_seed && key == qi)) t[r] = -INFINITY;
+        mx = fmax2(mx, t[r]);
+      }
+      mx = quad_max(mx);
+      const float mn = fmax2(m, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m - mn);
+      m = mn;
+      l *= alpha;
+#pragma unroll
+      for (int c = 0; c < DC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[c][e] *= alpha;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float pw = __builtin_amdgcn_exp2f(t[r] - m);
+        l += pw;
+#pragma unroll
+        for (int c = 0; c < DC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[c][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][c][e], pw, o[c][e], 0, 0, 0);
+      }
+#pragma unroll
+      for (int s = 0; s < KS; ++s) kf[s] = kn[s];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < DC; ++c) vf[r][c] = vn[r][c];
     }
-  }
-  if (qi < L) {
-    const float inv = 1.0f / l;
-    float* orow = p.out + b * p.q_sb + h * p.q_sh + (int64_t)qi * p.q_sl;
-#pragma unroll
-    for (int k = 0; k < D; k += 4) {
-      f32x4 v = {o[k] * inv, o[k + 1] * inv, o[k + 2] * inv, o[k + 3] * inv};
-      *(f32x4*)(orow + k) = v;
+    // ---- merge: accumulator (c, e) register r of lane (i, g) is O[query i][64 c + 16 g + 4 r + e]
+    l = quad_sum(l);
+    if (g4 == 0) {
+      sM[wave][i16] = m;
+      sL[wave][i16] = l;
     }
-    if (p.lse) p.lse[((int64_t)b * p.Hq + h) * L + qi] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *(f32x4*)&sO[wave][i16][64 * c + 16 * g4 + 4 * r] = f32x4{o[c][0][r], o[c][1][r], o[c][2][r], o[c][3][r]};
+    __syncthreads();
+    constexpr int CH = D / 4;  // lanes per query row, 4 columns each
+    for (int idx = tid; idx < kFT * CH; idx += nth) {
+      const int f = idx / CH, col = 4 * (idx % CH);
+      const int qr = qt * kFT + f;
+      if (qr >= L) continue;  // (whole rows: the CH lanes of a row leave together)
+      const bool sd = is_seed(qr);
+      float mm = kInitMax, td = -INFINITY;
+      f32x4 vd = {};
+      for (int w = 0; w < nw; ++w) mm = fmax2(mm, sM[w][f]);
+      if (sd) {
+        const f32x4 qv = *(const f32x4*)(qbase + (int64_t)qr * p.q_sl + col);
+        const f32x4 kd = *(const f32x4*)(p.kl + kvoff + (int64_t)qr * p.kv_sl + col);
+        vd = *(const f32x4*)(p.vl + kvoff + (int64_t)qr * p.kv_sl + col);
+        float dot = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(qv[e], kd[e], dot);
+#pragma unroll
+        for (int off = CH / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
+        td = dot * p.c2;
+        mm = fmax2(mm, td);
+      }
+      const float pd = __builtin_amdgcn_exp2f(td - mm);  // 0 unless the row is a seed
+      float den = pd;
+      f32x4 v = vd * pd;
+      for (int w = 0; w < nw; ++w) {
+        const float a = __builtin_amdgcn_exp2f(sM[w][f] - mm);
+        den = __builtin_fmaf(sL[w][f], a, den);
+        v += *(const f32x4*)&sO[w][f][col] * a;
+      }
+      const float inv = 1.0f / den;
+      *(f32x4*)(p.out + b * p.q_sb + h * p.q_sh + (int64_t)qr * p.q_sl + col) = v * inv;
+      if (p.lse && col == 0) p.lse[bh * L + qr] = (mm + __builtin_amdgcn_logf(den)) * kLn2;
+    }
+    __syncthreads();  // (the next tile rebuilds the bitmap and the slots)
   }
 }
 
@@ -796,16 +881,19 @@ hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream) {
   p.lse = a.lse;
   p.B = a.B; p.Hq = a.Hq; p.Hkv = a.Hkv; p.L = a.L; p.max_seeds = a.max_seeds;
   p.group = a.Hq / a.Hkv;
-  p.n_qt = (a.L + 63) / 64;
+  p.n_qt = (a.L + kFT - 1) / kFT;
   p.c2 = a.scale * 1.44269504088896341f;
   p.q_sb = a.q_sb; p.q_sh = a.q_sh; p.q_sl = a.q_sl;
   p.kv_sb = a.kv_sb; p.kv_sh = a.kv_sh; p.kv_sl = a.kv_sl;
-  const int64_t nwg = (int64_t)a.B * a.Hq * p.n_qt;
-  if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
+  p.n_wg = (int64_t)a.B * a.Hq * p.n_qt;
+  // a wave per key tile up to 8; past 2^20 tiles of queries a workgroup takes several
+  const int nw = (a.L + kFT - 1) / kFT;
+  const dim3 block(64u * (unsigned)(nw < kFWaves ? nw : kFWaves));
+  const dim3 grid((unsigned)(p.n_wg < (1 << 20) ? p.n_wg : (1 << 20)));
   if (a.d == 128)
-    hipLaunchKernelGGL(cover_attn_f32_kernel<128>, dim3((unsigned)nwg), dim3(64), 0, stream, p);
+    hipLaunchKernelGGL(cover_attn_f32_kernel<128>, grid, block, 0, stream, p);
   else
-    hipLaunchKernelGGL(cover_attn_f32_kernel<64>, dim3((unsigned)nwg), dim3(64), 0, stream, p);
+    hipLaunchKernelGGL(cover_attn_f32_kernel<64>, grid, block, 0, stream, p);
   return hipGetLastError();
 }
 

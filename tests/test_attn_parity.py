@@ -60,6 +60,37 @@ def test_f32_multi_tile_ragged(shape):
     check_attn(out, lse, ref, lref, torch.float32, str(shape))
 
 
+@pytest.mark.parametrize("L,d,n", [(15, 64, 3), (16, 128, 16), (17, 64, 2), (33, 128, 5), (127, 64, 9),
+                                   (129, 128, 20), (260, 64, 700)])
+def test_f32_tile_edges(L, d, n):
+    """One to eight waves per workgroup, whole and partial 16-row tiles, second tiles of a wave,
+    and a seed list longer than the positions fetched with its count."""
+    announce(f"fp32 L{L} d{d} seeds{n}")
+    a = _custom(L, 1, 2, 1, L, d, min(n, L), dtype="f32")
+    if n > L:  # the list's tail: entries outside [0, L), ignored
+        junk = torch.full((1, n - L), L + 7, dtype=torch.int32)
+        a["seed_idx"] = torch.cat([junk, a["seed_idx"][:, :L]], 1).contiguous()
+        a["n_seed"] = torch.full((1,), n, dtype=torch.int32)
+    out, lse = _run(a)
+    if n > L:
+        a["seed_idx"], a["n_seed"] = a["seed_idx"][:, n - L:].contiguous(), torch.full((1,), L, dtype=torch.int32)
+    ref, lref = _oracle(a)
+    check_attn(out, lse, ref, lref, torch.float32, f"L{L} d{d}")
+
+
+def test_f32_more_tiles_than_workgroups():
+    """Past 2^20 query tiles a workgroup takes several: one-token sequences, whose output is
+    their own value row."""
+    announce("fp32 B2^20+5 L1")
+    B = (1 << 20) + 5
+    x = torch.randn(B, 1, 1, 64, device="cuda")
+    out, lse = cover.cover_attn_fwd(x, x, x, x, x)
+    torch.cuda.synchronize()
+    assert torch.equal(out, x)
+    want = (x.double() ** 2).sum(-1) / 8.0
+    assert torch.allclose(lse.double(), want, rtol=1e-5, atol=1e-5)
+
+
 BF16_SHAPES = [
     (1, 2, 2, 64, 128, 4),
     (2, 4, 2, 300, 128, 12),
