@@ -216,9 +216,11 @@ def rect_splits(B: int, Hq: int, Lq: int, L: int) -> int:
     256 workgroups of at least 128 keys each, merged by a second launch)."""
     if L <= 2048 or B * Hq * ((Lq + 31) // 32) >= 256:
         return 1
-    wgs = B * Hq * ((Lq + 127) // 128)
-    n = min(-(-256 // wgs), -(-L // 128))
-    return max(1, min(n, 256))
+    tiles, stages = B * Hq * ((Lq + 31) // 32), -(-L // 32)
+    # rounds of 256 workgroups, each as long as its stages and about 18 stages' worth of start
+    # and merge; 24 for the second launch
+    cost = lambda n: -(-tiles * n // 256) * (-(-stages // n) + 18) + (24 if n > 1 else 0)
+    return min(range(1, min(256, -(-L // 128)) + 1), key=cost)
 
 
 def cover_attn_rect(q, k_live, v_live, k_cache, v_cache, q_off: int, seed_idx=None, n_seed=None,

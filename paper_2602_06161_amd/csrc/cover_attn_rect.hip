@@ -8,25 +8,18 @@
 // its diagonal (the leave-one-out view whose closed form App. B.4 gives).
 //
 // With few query rows the work is bound by reading K and V, not by the MFMAs, and one
-// workgroup per (row, 128-query tile) would leave most of the chip idle, so the keys are
-// split.  Two forms:
-//   * n_split == 1, cover_attn_tile_kernel (the default up to L = 2048): one launch, one
-//     workgroup of 8 waves per 32 query rows whose waves split the keys among themselves
-//     and merge in LDS (described at the kernel, below).
-//   * n_split > 1, two launches through the caller's workspace:
-//   kernel 1: one workgroup of 4 waves per (batch, query head, 128-query tile, key split).
-//     The waves share the split's K/V in LDS, loaded in groups of up to four 32-key stages
-//     (128 keys, 64 KiB) that are all requested at once, so a group costs one memory round
-//     trip; wave w owns 32 queries.  The Q rows and the seed list are requested together at
-//     the start.  S^T = K Q^T and O^T += V^T P^T
-//     on 32x32x16 bf16 MFMAs (Q as the B operand straight from registers, V^T by transposing
-//     LDS reads, P^T from the S^T registers), online softmax with the row max, row sums and
-//     O^T in fp32.  A seed row's cached diagonal score is dropped where it occurs and its
-//     live diagonal term is added by the split that holds the position.  Per row the split
-//     leaves its normalised output O / l in bf16 (256 bytes) and its max and sum in fp32 in
-//     the caller's workspace: the records are written and read once, so their size is
-//     traffic on top of K and V.
-//   * kernel 2: one wave per query row merges the splits and writes O and the lse.
+// workgroup per (row, 128-query tile) would leave most of the chip idle, so the keys are split:
+//   * n_split == 1 (the default up to L = 2048): one launch, one workgroup of 8 waves per 32
+//     query rows whose waves split the keys among themselves and merge in LDS (described at the
+//     kernel, below).
+//   * n_split > 1, two launches through the caller's workspace: the same kernel, a workgroup
+//     taking one of n_split ranges of the keys and leaving per row its normalised output O / l
+//     in bf16 (256 bytes) and its max and sum in fp32 (the records are written and read once, so
+//     their size is traffic on top of K and V); a seed row's live diagonal term is added by the
+//     split that holds the position.  Then one wave per query row merges the splits and writes O
+//     and the lse.  Against a kernel of 4 waves per 128 query rows that loaded 128 keys, waited,
+//     computed and loaded again (half its waves idle at 64 rows): B1 Hq32/Hkv8 L8192, 64 rows,
+//     38.3 -> 22.4 us; L16000, 8 rows, 62 -> 21; B1 H12 L12000, 180 rows, 56 -> 32.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -49,9 +42,6 @@ typedef __attribute__((address_space(1))) const char gmem_t;
 constexpr int kD = 128;
 constexpr int kRow = 2 * kD;            // bytes per K/V row
 constexpr int kStage = 32;              // keys per stage
-constexpr int kGroup = 4;               // stages loaded together
-constexpr int kThreads = 256;           // 4 waves
-constexpr int kQT = 128;                // queries per workgroup
 constexpr int kMaxWords = COVER_MAX_L / 32;
 constexpr float kInit = -1.0e30f;       // finite "nothing seen yet" max
 constexpr float kLn2 = 0.693147180559945309f;
@@ -68,9 +58,11 @@ struct RectParams {
   __bf16* out;
   float* lse;
   int B, Hq, Hkv, L, Lq, q_off, max_seeds, group, n_qt, n_split, split_stages;
-  int n_wg, xcd_slots;  // single-launch form: workgroups, logical tiles per XCD
+  int n_wg, xcd_slots;  // workgroups of the launch, and of them per XCD
   float c2;  // scale * log2(e)
   int64_t q_sb, q_sh, q_sl, kv_sb, kv_sh, kv_sl;
+  // key splits: first workgroup of the launch; key rows too far apart for 32-bit offsets in a stage
+  int first_wg, wide;
 };
 
 // LDS layouts: K rows with the 16-byte chunk index XOR-ed by row % 16 (a b128 operand read of
@@ -93,250 +85,6 @@ __device__ __forceinline__ float pair_sum(float x) {
 
 __device__ __forceinline__ i16x4 v_tr(const lds_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)p);
-}
-
-__global__ __launch_bounds__(kThreads, 2) void cover_attn_rect_kernel(const RectParams p) {
-  __shared__ __attribute__((aligned(16))) char sK[kGroup][kStage * kRow];
-  __shared__ __attribute__((aligned(16))) char sV[kGroup][kStage * kRow];
-  __shared__ uint32_t bm[kMaxWords];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, hl = lane >> 5;
-  int id = blockIdx.x;
-  const int qt = id % p.n_qt;
-  id /= p.n_qt;
-  const int split = id % p.n_split;
-  const int bh = id / p.n_split;
-  const int b = bh / p.Hq, h = bh % p.Hq, hk = h / p.group;
-
-  // this wave's queries (requested first: nothing below depends on them until the MFMAs)
-  const int qrow0 = qt * kQT + wave * 32;
-  const bool active = qrow0 < p.Lq;
-  const int qrow = min(qrow0 + l32, p.Lq - 1);
-  const int pos = p.q_off + qrow;
-  const __bf16* qp = p.q + b * p.q_sb + h * p.q_sh + (int64_t)qrow * p.q_sl;
-  bf16x8 qreg[kD / 16];
-#pragma unroll
-  for (int ks = 0; ks < kD / 16; ++ks)
-    qreg[ks] = *(const bf16x8*)(qp + (2 * ks + hl) * 8);
-
-  // seed bitmap of the whole sequence; the count and the list are requested together
-  const int nW = (p.L + 31) >> 5;
-  for (int w = tid; w < nW; w += kThreads) bm[w] = 0u;
-  __syncthreads();
-  if (p.max_seeds > 0) {
-    int ns = p.n_seed[b];
-    ns = ns < 0 ? 0 : (ns > p.max_seeds ? p.max_seeds : ns);
-    for (int t = tid; t < p.max_seeds; t += kThreads) {
-      const int j = p.seed_idx[(int64_t)b * p.max_seeds + t];
-      if (t < ns && j >= 0 && j < p.L) atomicOr(&bm[j >> 5], 1u << (j & 31));
-    }
-  }
-  __syncthreads();
-  auto is_seed = [&](int j) { return (bm[j >> 5] >> (j & 31)) & 1u; };
-  const bool row_seed = is_seed(pos);
-
-  // key range of this split
-  const int k_begin = split * p.split_stages * kStage;
-  const int k_end = min(p.L, k_begin + p.split_stages * kStage);
-  const int n_st = k_end > k_begin ? (k_end - k_begin + kStage - 1) / kStage : 0;
-
-  // cooperative group loads: per stage 512 chunks of 16 bytes of K (and of V), two per
-  // thread; every stage of a group is requested before the first is stored
-  const int64_t kvbase = b * p.kv_sb + hk * p.kv_sh;
-  auto load_group = [&](int st0, int n) {
-    u32x4 kr[kGroup][2], vr[kGroup][2];
-#pragma unroll
-    for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int c = tid * 2 + u, row = c >> 4, ch = c & 15;
-        const int key = k_begin + (st0 + g) * kStage + row;
-        kr[g][u] = vr[g][u] = u32x4{0u, 0u, 0u, 0u};
-        if (g < n && key < k_end) {
-          const int64_t off = kvbase + (int64_t)key * p.kv_sl + ch * 8;
-          const bool sd = is_seed(key);
-          kr[g][u] = *(const u32x4*)((sd ? p.kc : p.kl) + off);
-          vr[g][u] = *(const u32x4*)((sd ? p.vc : p.vl) + off);
-        }
-      }
-#pragma unroll
-    for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int c = tid * 2 + u, row = c >> 4, ch = c & 15;
-        if (g < n) {
-          *(u32x4*)(sK[g] + k_off(row, ch)) = kr[g][u];
-          *(u32x4*)(sV[g] + v_chunk(row, ch)) = vr[g][u];
-        }
-      }
-  };
-
-  // V^T operand addresses: lane (G = lane / 16, i = lane % 16) reads keys
-  // 16 kk + {0..3, 8..11} + 4 (G / 2) of d-block db, the key order of the S^T registers
-  uint32_t vaddr[kD / 32];
-  {
-    const int G = lane >> 4, ii = lane & 15;
-    const int row = 4 * (G >> 1) + (ii >> 2);
-#pragma unroll
-    for (int db = 0; db < kD / 32; ++db) vaddr[db] = v_elem(row, db * 32 + 16 * (G & 1) + 4 * (ii & 3));
-  }
-
-  f32x16 o[kD / 32];
-#pragma unroll
-  for (int db = 0; db < kD / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
-  float m = kInit, l = 0.0f;
-
-  // Two 32-key stages per pass (they are in the same group: groups start at multiples of
-  // four stages): two independent S^T chains, one softmax over both, and every LDS operand of
-  // the pass requested before its first MFMA (one LDS latency per pass).  The running max is
-  // raised lazily, once some row's scores exceed it by 2^8 (weights up to 256 stay exact
-  // enough in bf16 and far from fp32 overflow), so O is rarely rescaled; the first pass sets
-  // it while O and the sums are still zero.
-  constexpr float kLazy = 8.0f;
-  for (int st = 0; st < n_st; st += 2) {
-    const int buf = st % kGroup;
-    if (buf == 0) {
-      if (st > 0) __syncthreads();  // every wave is done with the previous group
-      load_group(st, min(kGroup, n_st - st));
-      __syncthreads();
-    }
-    const bool two = st + 1 < n_st;
-    if (active) {
-      bf16x8 ka[2][kD / 16], va[2][2][kD / 32];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        const lds_t* kb = (const lds_t*)sK[buf + (two ? kt : 0)];
-        const lds_t* vb = (const lds_t*)sV[buf + (two ? kt : 0)];
-#pragma unroll
-        for (int ks = 0; ks < kD / 16; ++ks)
-          ka[kt][ks] = *(const __attribute__((address_space(3))) bf16x8*)(kb + k_off(l32, 2 * ks + hl));
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int db = 0; db < kD / 32; ++db) {
-            const lds_t* base = vb + vaddr[db] + kk * 16 * kRow;
-            va[kt][kk][db] = __builtin_bit_cast(
-                bf16x8, __builtin_shufflevector(v_tr(base), v_tr(base + 8 * kRow), 0, 1, 2, 3, 4, 5, 6, 7));
-          }
-      }
-      f32x16 sc[2];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sc[kt][r] = 0.0f;
-#pragma unroll
-      for (int ks = 0; ks < kD / 16; ++ks)
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-          sc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kt][ks], qreg[ks], sc[kt], 0, 0, 0);
-      // register r of stage kt holds key k0 + 32 kt + 8 (r / 4) + 4 hl + r % 4 of row qrow
-      const int k0 = k_begin + st * kStage;
-      const bool edge = k0 + 2 * kStage > k_end;  // keys past the split's end (or no stage 2)
-      const bool diag = row_seed && pos >= k0 && pos < k0 + 2 * kStage;
-      float mx = kInit;
-      if (__builtin_amdgcn_ballot_w64(diag) != 0 || edge) {
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = k0 + 32 * kt + 8 * (r >> 2) + 4 * hl + (r & 3);
-            float t = sc[kt][r] * p.c2;
-            if (key >= k_end || (diag && key == pos)) t = -INFINITY;
-            sc[kt][r] = t;
-            mx = __builtin_fmaxf(mx, t);
-          }
-      } else {
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            sc[kt][r] *= p.c2;
-            mx = __builtin_fmaxf(mx, sc[kt][r]);
-          }
-      }
-      mx = pair_max(mx);
-      if (st == 0) {
-        m = mx;
-      } else if (__builtin_amdgcn_ballot_w64(mx > m + kLazy)) {
-        const float mn = __builtin_fmaxf(m, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m - mn);
-        l *= alpha;
-#pragma unroll
-        for (int db = 0; db < kD / 32; ++db) o[db] *= alpha;
-        m = mn;
-      }
-      bf16x8 pk[2][2];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float pr = __builtin_amdgcn_exp2f(sc[kt][8 * kk + e] - m);
-            l += pr;
-            pk[kt][kk][e] = (__bf16)pr;
-          }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-        for (int db = 0; db < kD / 32; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0][kk][db], pk[0][kk], o[db], 0, 0, 0);
-      if (two) {  // (a lone last stage: its second half is all masked, and its buffer stale)
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int db = 0; db < kD / 32; ++db)
-            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1][kk][db], pk[1][kk], o[db], 0, 0, 0);
-      }
-    }
-  }
-
-  if (!active) return;
-  // the live diagonal term of a seed row, in the split that holds its position
-  if (row_seed && pos >= k_begin && pos < k_end) {
-    const __bf16* kp = p.kl + kvbase + (int64_t)pos * p.kv_sl;
-    float dot = 0.0f;
-#pragma unroll
-    for (int ks = 0; ks < kD / 16; ++ks) {
-      const bf16x8 kv8 = *(const bf16x8*)(kp + (2 * ks + hl) * 8);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dot = __builtin_fmaf((float)qreg[ks][e], (float)kv8[e], dot);
-    }
-    dot = pair_sum(dot);
-    const float t = dot * p.c2;
-    const float mn = __builtin_fmaxf(m, t);
-    const float alpha = __builtin_amdgcn_exp2f(m - mn);
-    m = mn;
-    const float pd = __builtin_amdgcn_exp2f(t - m);
-    l = l * alpha + (hl == 0 ? pd : 0.0f);
-    const __bf16* vp = p.vl + kvbase + (int64_t)pos * p.kv_sl;
-#pragma unroll
-    for (int db = 0; db < kD / 32; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int dim = 32 * db + 8 * g + 4 * hl;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[db][4 * g + e] = __builtin_fmaf(pd, (float)vp[dim + e], o[db][4 * g + e] * alpha);
-      }
-  }
-  const float lt = pair_sum(l);
-  if (qrow0 + l32 >= p.Lq) return;
-  float* rec = p.ws + (((int64_t)bh * p.n_split + split) * p.Lq + qrow0 + l32) * COVER_RECT_RECORD;
-  const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-#pragma unroll
-  for (int db = 0; db < kD / 32; ++db)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *(bf16x4*)((__bf16*)rec + 32 * db + 8 * g + 4 * hl) =
-          bf16x4{(__bf16)(o[db][4 * g] * inv), (__bf16)(o[db][4 * g + 1] * inv),
-                 (__bf16)(o[db][4 * g + 2] * inv), (__bf16)(o[db][4 * g + 3] * inv)};
-  if (hl == 0) {
-    rec[kD / 2] = m;
-    rec[kD / 2 + 1] = lt;
-  }
 }
 
 // One wave per query row: merge the splits' (max, sum, O / sum), write O (bf16) and the lse.
@@ -471,6 +219,8 @@ __device__ uint64_t g_rect_times[kTimeWG * kTW * kTimeSlots];
 #define RECT_TSTAMP(slot) do {} while (0)
 #endif
 
+// SPLIT: key splits (records for the merge kernel); otherwise the whole of a row's keys
+template <bool SPLIT>
 __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const RectParams p) {
   // per wave: a K slot and a V slot (at the end: its partial O, 32 rows of 128 fp32);
   // the tile's Q; the seed bitmap of the sequence; the seed list; the partial maxima and sums
@@ -489,17 +239,30 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
   const int li = (blockIdx.x & 7) * p.xcd_slots + (blockIdx.x >> 3);
   if (li >= p.n_wg) return;
   RECT_TSTAMP(0);
-  const int qt = li % p.n_qt, bh = li / p.n_qt;
-  const int h = bh % p.Hq, b = bh / p.Hq, g = h / p.group;
+  int split = 0, h, b;
+  const int id = SPLIT ? p.first_wg + li : li;
+  const int qt = id % p.n_qt;
+  int bh = id / p.n_qt;
+  if constexpr (SPLIT) {  // tile fastest, then the query heads of a KV head, then its key splits
+    const int hg = bh % p.group, rest = bh / p.group, kv = rest / p.n_split;
+    split = rest % p.n_split;
+    bh = kv * p.group + hg;
+  }
+  h = bh % p.Hq;
+  b = bh / p.Hq;
+  const int g = h / p.group;
   const int L = p.L;
-  const int nst = (L + kStage - 1) / kStage;
+  // this workgroup's 32-key stages [sb, sb + nst) (all of them without key splits)
+  const int n_stages = (L + kStage - 1) / kStage;
+  const int sb = SPLIT ? split * p.split_stages : 0;
+  const int nst = SPLIT ? max(min(n_stages - sb, p.split_stages), 0) : n_stages;
   // this wave's stages: waves 0-3 take 10/64 of them each, waves 4-7 (the second wave of
   // each SIMD, which loses the load path's arbitration to the first) 6/64: the measured
   // split that lets the waves finish together
   const int cw0 = wave < 4 ? 10 * wave : 40 + 6 * (wave - 4);
   const int cw1 = wave < 3 ? 10 * (wave + 1) : 40 + 6 * (wave - 3);
-  const int s0 = nst * cw0 / 64, s1 = nst * cw1 / 64;
-  const int ragged = L % kStage ? nst - 1 : -1;
+  const int s0 = sb + nst * cw0 / 64, s1 = sb + nst * cw1 / 64;
+  const int ragged = L % kStage ? n_stages - 1 : -1;
   const int nW = (L + 31) >> 5;
   for (int w = tid; w < nW; w += 64 * kTW) bits[w] = 0u;
 
@@ -524,7 +287,7 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
   // row from the cache; rows past L clamped into the sequence
   auto ld_stage = [&](uint32_t slot, const char* live, const char* cache, const uint32_t* off, int st,
                       uint32_t seeds) __attribute__((always_inline)) {
-    if (st == ragged || seeds != 0u) {
+    if (st == ragged || seeds != 0u || (SPLIT && p.wide)) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int row = 4 * j + (lane >> 4);
@@ -548,6 +311,10 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
                    __attribute__((always_inline)) {
     const uint32_t w = seed_word(st);
     if (w == 0u) return;
+    if (SPLIT && p.wide) {  // (the 32-bit offsets below do not reach: every row by its own address)
+      ld_stage(slot, cache == kcc ? klc : vlc, cache, off, st, w);
+      return;
+    }
     gmem_t* base = uniform_ptr(cache + st * stage_bytes);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -613,7 +380,9 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
   const int fq = lane >> 4, fj = lane & 15;
   const int qfin = qt * kTQ + kFin * wave + fq;
   const bool fin_ok = qfin < p.Lq;
-  const bool fseed = fin_ok && is_seed(p.q_off + qfin);
+  // (with key splits the diagonal term belongs to the split that holds the position)
+  const int fstage = (p.q_off + qfin) / kStage;
+  const bool fseed = fin_ok && (!SPLIT || (fstage >= sb && fstage < sb + nst)) && is_seed(p.q_off + qfin);
   u32x4 kd = {0u, 0u, 0u, 0u}, vd = {0u, 0u, 0u, 0u};
   if (fseed) {
     const int64_t ro = kvoff + (int64_t)(p.q_off + qfin) * p.kv_sl + 8 * fj;
@@ -795,7 +564,18 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
         acc[2 * e + 1] = __builtin_fmaf(pd, __uint_as_float(vd[e] & 0xffff0000u), acc[2 * e + 1]);
       }
     }
-    if (fin_ok) {
+    if (SPLIT && fin_ok) {  // the split's record: O / sum in bf16, the max and the sum
+      float* rec = p.ws + (((int64_t)bh * p.n_split + split) * p.Lq + qfin) * COVER_RECT_RECORD;
+      const float inv = den > 0.0f ? 1.0f / den : 0.0f;
+      bf16x8 ob;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(acc[e] * inv);
+      *(bf16x8*)((__bf16*)rec + 8 * fj) = ob;
+      if (fj == 0) {
+        rec[kD / 2] = M;
+        rec[kD / 2 + 1] = den;
+      }
+    } else if (fin_ok) {
       const float inv = 1.0f / den;
       bf16x8 ob;
 #pragma unroll
@@ -828,24 +608,29 @@ hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
   p.out = (__bf16*)a.out; p.lse = a.lse;
   p.B = a.B; p.Hq = a.Hq; p.Hkv = a.Hkv; p.L = a.L; p.Lq = a.Lq; p.q_off = a.q_off;
   p.max_seeds = a.max_seeds; p.group = a.Hq / a.Hkv;
-  p.n_qt = (a.Lq + kQT - 1) / kQT;
+  p.n_qt = (a.Lq + kTQ - 1) / kTQ;
   p.n_split = a.n_split;
   const int stages = (a.L + kStage - 1) / kStage;
   p.split_stages = (stages + a.n_split - 1) / a.n_split;
   p.c2 = a.scale * 1.44269504088896341f;
   p.q_sb = a.q_sb; p.q_sh = a.q_sh; p.q_sl = a.q_sl;
   p.kv_sb = a.kv_sb; p.kv_sh = a.kv_sh; p.kv_sl = a.kv_sl;
-  if (a.n_split == 1) {  // single launch, no workspace (kv_sl < 2^26: 32-bit in-stage offsets)
-    p.n_qt = (a.Lq + kTQ - 1) / kTQ;
-    const int64_t n = (int64_t)a.B * a.Hq * p.n_qt;
+  p.wide = a.kv_sl >= (int64_t(1) << 26);
+  const int64_t n = (int64_t)a.B * a.Hq * p.n_qt * a.n_split;
+  const dim3 block(64 * kTW);
+  if (a.n_split == 1) {
     p.n_wg = (int)n;
     p.xcd_slots = (int)((n + 7) / 8);
-    hipLaunchKernelGGL(cover_attn_tile_kernel, dim3((unsigned)(8 * (int64_t)p.xcd_slots)), dim3(64 * kTW), 0,
-                       stream, p);
+    hipLaunchKernelGGL(cover_attn_tile_kernel<false>, dim3((unsigned)(8 * (int64_t)p.xcd_slots)), block, 0, stream, p);
     return hipGetLastError();
   }
-  const int64_t nwg = (int64_t)a.B * a.Hq * p.n_qt * a.n_split;
-  hipLaunchKernelGGL(cover_attn_rect_kernel, dim3((unsigned)nwg), dim3(kThreads), 0, stream, p);
+  constexpr int64_t kMaxGrid = (int64_t(1) << 23) - 8;  // workgroups per launch: under 2^32 work-items
+  for (int64_t first = 0; first < n; first += kMaxGrid) {
+    p.first_wg = (int)first;
+    p.n_wg = (int)(n - first < kMaxGrid ? n - first : kMaxGrid);
+    p.xcd_slots = (p.n_wg + 7) / 8;
+    hipLaunchKernelGGL(cover_attn_tile_kernel<true>, dim3((unsigned)(8 * p.xcd_slots)), block, 0, stream, p);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t rows = (int64_t)a.B * a.Hq * a.Lq;
