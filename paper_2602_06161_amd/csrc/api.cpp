@@ -80,8 +80,7 @@ cover_status cover_attn_fwd(const void* q, const void* k_live, const void* v_liv
     if (e != hipSuccess) return COVER_ERR_HIP;
   }
   if (D.dtype != COVER_BF16) return hip_status(cover::launch_attn_f32(a, stream));
-  if (D.d == 128) return hip_status(cover::launch_attn_bf16_w4(a, stream));
-  return hip_status(cover::launch_attn_bf16(a, stream));  // d = 64
+  return hip_status(cover::launch_attn_bf16(a, stream));
 }
 
 cover_status cover_select_seeds(const float* logp, const float* d_in, const float* d_out,

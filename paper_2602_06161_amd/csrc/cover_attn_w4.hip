@@ -1,10 +1,10 @@
-// COVER attention on gfx950, head dimension 128, bf16: four waves per workgroup, one per SIMD.
+// COVER attention on gfx950, bf16, head dimension 128 or 64: four waves per workgroup.
 //
-// Same operation as the eight-wave kernel (arXiv 2602.06161, Sec. 5.1 "KV cache override" and
-// "Diagonal correction"; App. B): for query row i of batch row b with seed set S_b,
+// The operation (arXiv 2602.06161, Sec. 5.1 "KV cache override" and "Diagonal correction";
+// App. B): for query row i of batch row b with seed set S_b,
 //   K'_j = k_cache_j if j in S_b else k_live_j (V' likewise); row i attends to K' except that a
 //   seed row sees its own live key/value on the diagonal; out_i = softmax(scale q_i K^(i)) V^(i).
-// The diagonal is handled as in the eight-wave kernel: the cached diagonal score of a seed row
+// The cached diagonal score of a seed row
 // gets no weight in the main loop, and the live diagonal term exp(scale q_i.k_live_i) v_live_i
 // joins the row's softmax in the epilogue (exactly the leave-one-out row of App. B.1, with no
 // division by the closed form's r_i).
@@ -16,8 +16,13 @@
 //     A wave owns two 32-query tiles, so every K or V^T operand read from LDS feeds two MFMAs:
 //     a stage costs the workgroup 64 KiB of LDS reads (the transposing V read delivers about a
 //     third of the bandwidth of a plain 16-byte read), not 128 KiB.
-//   * The 128 O^T accumulators per lane and Q live in AGPRs (one wave per SIMD has 512
-//     registers); S, P and the operands read from LDS stay in VGPRs.
+//   * D = 128: the 128 O^T accumulators per lane and Q live in AGPRs (one wave per SIMD has 512
+//     registers); S, P and the operands read from LDS stay in VGPRs.  D = 64 needs 230 registers
+//     and 77 KB of LDS, so two workgroups share a CU and one's softmax runs beside the other's
+//     MFMAs: there a 64-key stage has 512 cycles of MFMA work per SIMD and about as much of
+//     softmax, and a single wave cannot hide one behind the other.  Against a kernel of eight
+//     waves with one 32-query tile each (every operand read from LDS feeding one MFMA), B4 H16
+//     L1001 d64, 24 seeds: 39.5 -> 27.2 us (1.85k cycles per pair of stages).
 //   * Every global load goes straight to LDS (global_load_lds_dwordx4): the seed list, Q (read
 //     into registers once), the live rows of a seeded tile's diagonal (with the last step, into
 //     the Q area), and K/V stages in three buffers each, issued two stages ahead and
@@ -54,26 +59,31 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) char lds_t;
 typedef __attribute__((address_space(1))) const char gmem_t;
 
-constexpr int kD = 128;
-constexpr int kRow = 2 * kD;                 // bytes per K/V/Q row
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBM = 128;                     // queries per workgroup
 constexpr int kStage = 64;                   // keys per stage
-constexpr int kSBytes = kStage * kRow;       // one K or V stage buffer (16 KiB)
-constexpr int kLoads = kSBytes / 1024 / kWaves;  // 1-KiB loads per wave per stage buffer
-constexpr int kKS = kD / 16;                 // k-steps of S^T = K Q^T
-constexpr int kDB = kD / 32;                 // 32-row blocks of O^T
 constexpr int kSeedsLds = kThreads;          // seed positions staged in LDS (more: read directly)
 constexpr float kInitMax = -1.0e30f;         // finite "no key seen yet" reference max
 constexpr float kBig = 16777216.0f;          // 2^24
 constexpr float kLn2 = 0.693147180559945309f;
-static_assert(kLoads == 4, "a stage gives every wave four 1-KiB loads");
 
 // s_waitcnt immediates that wait for vmcnt <= n only (lgkmcnt and expcnt untouched)
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x70 | 0xf00; }
-// at the top of a step the eight loads of the previous step may stay in flight
-constexpr int kWaitStep = vmcnt_imm(2 * kLoads);
+
+template <int D>
+struct Geo {
+  static constexpr int kRow = 2 * D;                       // bytes per K/V/Q row
+  static constexpr int kCh = kRow / 16;                    // 16-byte chunks per row
+  static constexpr int kRPL = 1024 / kRow;                 // rows per 1-KiB load
+  static constexpr int kSBytes = kStage * kRow;            // one K or V stage buffer
+  static constexpr int kLoads = kSBytes / 1024 / kWaves;   // 1-KiB loads per wave per stage buffer
+  static constexpr int kKS = D / 16;                       // k-steps of S^T = K Q^T
+  static constexpr int kDB = D / 32;                       // 32-row blocks of O^T
+  // at the top of a step the loads of the previous step may stay in flight
+  static constexpr int kWaitStep = vmcnt_imm(2 * kLoads);
+  static_assert(kLoads == kDB && 2 * kLoads == kKS, "one load per d-block and per two k-steps");
+};
 
 struct Params4 {
   const __bf16* q;
@@ -91,36 +101,54 @@ struct Params4 {
 };
 
 // LDS swizzles (64 banks of 4 bytes).  K and Q rows: the 16-byte chunk index is XOR-ed with
-// row % 16, so the 32 rows of one b128 operand read spread over all banks.  V rows: the chunk
-// index is XOR-ed with 4 * (row % 4), so one transposing read (8 rows x 64 bytes) covers every
-// bank exactly twice.
-__device__ __forceinline__ int k_swz(int row) { return row & 15; }
-__device__ __forceinline__ int v_swz(int row) { return (row & 3) << 2; }
-__device__ __forceinline__ uint32_t k_off(int row, int c) { return row * kRow + ((c ^ k_swz(row)) << 4); }
+// row % 16 (D = 128) or row / 2 % 8 (D = 64: two rows per 256-byte window), so the 32 rows of
+// one b128 operand read spread over all banks.  V rows: the chunk index is XOR-ed with
+// 4 * (row % 4) (2 * (row % 4)), so one transposing read (8 rows x 64 bytes) covers every bank
+// exactly twice.
+template <int D>
+__device__ __forceinline__ int k_swz(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+template <int D>
+__device__ __forceinline__ int v_swz(int row) { return (row & 3) << (D == 128 ? 2 : 1); }
+template <int D>
+__device__ __forceinline__ uint32_t k_off(int row, int c) { return row * (2 * D) + ((c ^ k_swz<D>(row)) << 4); }
+template <int D>
 __device__ __forceinline__ uint32_t v_elem(int row, int col) {
-  return row * kRow + (((col >> 3) ^ v_swz(row)) << 4) + ((col & 7) << 1);
+  return row * (2 * D) + (((col >> 3) ^ v_swz<D>(row)) << 4) + ((col & 7) << 1);
 }
 
-// The MFMAs are written as inline assembly so that the register class of every operand is
-// fixed: S in VGPRs (read by the softmax), O and Q in AGPRs.  The compiler does not see these
-// as MFMAs, so the few places where VALU code reads an MFMA result soon after it was written
-// wait explicitly (mfma_drain), and VALU-written operands are separated from their MFMA
-// (valu_to_mfma).
+// At D = 128 (one wave per SIMD) the MFMAs are written as inline assembly so that the register
+// class of every operand is fixed: S in VGPRs (read by the softmax), O and Q in AGPRs.  The
+// compiler does not see these as MFMAs, so the few places where VALU code reads an MFMA result
+// soon after it was written wait explicitly (mfma_drain), and VALU-written operands are
+// separated from their MFMA (valu_to_mfma).  At D = 64 (two waves per SIMD, 256 registers)
+// nothing needs AGPRs and the builtins, with the compiler's own waits, do.
+template <int D>
 __device__ __forceinline__ void mfma_first(f32x16& d, bf16x8 a, bf16x8 qb) {  // d = a q
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(qb));
+  if constexpr (D == 128) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "a"(qb));
+  else d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb, (f32x16){}, 0, 0, 0);
 }
+template <int D>
 __device__ __forceinline__ void mfma_v(f32x16& d, bf16x8 a, bf16x8 qb) {  // d += a q (VGPR)
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(qb));
+  if constexpr (D == 128) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "a"(qb));
+  else d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb, d, 0, 0, 0);
 }
-__device__ __forceinline__ void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {  // d += a b (AGPR)
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+template <int D>
+__device__ __forceinline__ void mfma_a(f32x16& d, bf16x8 a, bf16x8 b) {  // d += a b (D = 128: AGPR)
+  if constexpr (D == 128) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+  else d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, d, 0, 0, 0);
 }
 // wait until every issued MFMA has written its result (the 8-pass 32x32x16 MFMA needs at
 // most 18 wait states before a dependent VALU read; 3 x 8 are given)
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory"); }
+template <int D>
+__device__ __forceinline__ void mfma_drain() {
+  if constexpr (D == 128) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+}
 // VALU-written operands need 2 wait states before an MFMA reads them; tying the nop to the
 // operand orders it after the write and before the read
-__device__ __forceinline__ void valu_to_mfma(bf16x8& x) { asm("s_nop 1" : "+v"(x)); }
+template <int D>
+__device__ __forceinline__ void valu_to_mfma(bf16x8& x) {
+  if constexpr (D == 128) asm("s_nop 1" : "+v"(x));
+}
 __device__ __forceinline__ u32x4 lds_read16(const lds_t* p) {
   return *(const __attribute__((address_space(3))) u32x4*)p;
 }
@@ -156,11 +184,19 @@ __device__ __forceinline__ void dma16m(uint32_t lds, gmem_t* base, uint32_t voff
                "global_load_lds_dwordx4 %3, %4\n\ts_mov_b64 exec, %0"
                : "=&s"(save) : "s"(mask), "s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
-// lanes 16 k .. 16 k + 15 for each set bit k of a 4-bit value
-__device__ __forceinline__ uint64_t lane_quads(uint32_t n) {
-  const uint64_t m = (uint64_t)(n & 1u) | ((uint64_t)(n & 2u) << 15) | ((uint64_t)(n & 4u) << 30) |
-                     ((uint64_t)(n & 8u) << 45);
-  return (m << 16) - m;
+// the lanes that load row k, for each set bit k: 16 k .. 16 k + 15 of 4 rows (D = 128), or
+// 8 k .. 8 k + 7 of 8 rows (D = 64; the product puts bit k of a nibble at 8 k)
+template <int D>
+__device__ __forceinline__ uint64_t lane_rows(uint32_t n) {
+  if constexpr (D == 128) {
+    const uint64_t m = (uint64_t)(n & 1u) | ((uint64_t)(n & 2u) << 15) | ((uint64_t)(n & 4u) << 30) |
+                       ((uint64_t)(n & 8u) << 45);
+    return (m << 16) - m;
+  } else {
+    const uint64_t m = (uint64_t)(((n & 15u) * 0x00204081u) & 0x01010101u) |
+                       ((uint64_t)(((n >> 4) * 0x00204081u) & 0x01010101u) << 32);
+    return (m << 8) - m;
+  }
 }
 __device__ __forceinline__ void dma4(uint32_t lds, gmem_t* addr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
@@ -224,7 +260,10 @@ __device__ uint64_t g_attn_times[kTimeWG * kWaves * kTimeSlots];
 #define COVER_TREAL(slot) do {} while (0)
 #endif
 
-__global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params4 p) {
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void cover_attn_w4_kernel(const Params4 p) {
+  constexpr int kRow = Geo<D>::kRow, kCh = Geo<D>::kCh, kRPL = Geo<D>::kRPL, kSBytes = Geo<D>::kSBytes;
+  constexpr int kLoads = Geo<D>::kLoads, kKS = Geo<D>::kKS, kDB = Geo<D>::kDB, kWaitStep = Geo<D>::kWaitStep;
   // Three K and three V stage buffers; Q of the workgroup on its way to registers (later: the
   // live rows of the seed rows' diagonals, then the output tiles); the seed list, the seed
   // bitmap of the sequence and its per-stage summary; merge scalars; the recompute flag.
@@ -269,13 +308,13 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
   const int64_t sbase = (int64_t)b * p.max_seeds;
 
   // ---- load geometry -------------------------------------------------------------------
-  // Load j of this wave covers stage rows (wave * 4 + j) * 4 + lane / 16, physical chunk
-  // lane % 16 (logical chunk = physical ^ swizzle), landing at byte (wave * 4 + j) * 1024 +
-  // 16 lane of the stage buffer, which is where the swizzled layout wants it.
-  auto ld_row = [&](int j) __attribute__((always_inline)) { return (wave * kLoads + j) * 4 + (lane >> 4); };
+  // Load j of this wave covers stage rows (wave * kLoads + j) * kRPL + lane / kCh, physical
+  // chunk lane % kCh (logical chunk = physical ^ swizzle), landing at byte (wave * kLoads + j) *
+  // 1024 + 16 lane of the stage buffer, which is where the swizzled layout wants it.
+  auto ld_row = [&](int j) __attribute__((always_inline)) { return (wave * kLoads + j) * kRPL + lane / kCh; };
   auto ld_chunk = [&](int j, bool is_v) __attribute__((always_inline)) -> uint32_t {
-    const int row = ld_row(j), pc = lane & 15;
-    return (uint32_t)((pc ^ (is_v ? v_swz(row) : k_swz(row))) << 4);
+    const int row = ld_row(j), pc = lane % kCh;
+    return (uint32_t)((pc ^ (is_v ? v_swz<D>(row) : k_swz<D>(row))) << 4);
   };
   const int64_t row_bytes = p.kv_sl * 2;
   const int64_t stage_bytes = kStage * row_bytes;
@@ -312,13 +351,13 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
       dma4(lds_u32((lds_t*)sSeeds + 256 * wave), (gmem_t*)(p.seed_idx + sbase + e));
   }
   ld_live(kbuf(0), klb, false, 0);
-  // Q rows q0 + r (r = 32 wave + 4 j + lane / 16), rows past L clamped, K swizzle
+  // Q rows q0 + r (r = 32 wave + kRPL j + lane / kCh), rows past L clamped, K swizzle
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int r = 32 * wave + 4 * j + (lane >> 4), pc = lane & 15;
+  for (int j = 0; j < 32 / kRPL; ++j) {
+    const int r = 32 * wave + kRPL * j + lane / kCh, pc = lane % kCh;
     const int qi = min(q0 + r, L - 1);
-    dma16(lds_u32((lds_t*)sQ + (32 * wave + 4 * j) * kRow),
-          (gmem_t*)(qbase + (int64_t)qi * p.q_sl) + ((pc ^ k_swz(r)) << 4));
+    dma16(lds_u32((lds_t*)sQ + (32 * wave + kRPL * j) * kRow),
+          (gmem_t*)(qbase + (int64_t)qi * p.q_sl) + ((pc ^ k_swz<D>(r)) << 4));
   }
   // words past the sequence are cleared too: per-stage lookups read two words per stage
   for (int w = tid; w < 2 * n_it; w += kThreads) bits[w] = 0u;
@@ -329,7 +368,10 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int db = 0; db < kDB; ++db) asm volatile("; O = 0" : "=a"(o[t][db]) : "0"((f32x16){}));
+    for (int db = 0; db < kDB; ++db) {
+      if constexpr (D == 128) asm volatile("; O = 0" : "=a"(o[t][db]) : "0"((f32x16){}));
+      else o[t][db] = (f32x16){};
+    }
   // the seed list, K(0) and Q have landed; the next stages go out only now, so that Q and
   // K(0) do not share the vector-memory path with them at the start of the kernel (V(0) and
   // K(1) are first needed at the top of step 0)
@@ -429,10 +471,11 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
   // Reload the rows of a stage that the uniform loads got wrong: in the ragged last stage the
   // rows below L (from the live tensor), and every seed row (from the cache).  Issued after
   // the uniform loads of the same wave, so these land last; load j takes the lanes of rows
-  // 16 wave + 4 j + {0..3} that need it (lane / 16 selects the row), and is skipped if there
+  // 16 wave + kRPL j + {0 .. kRPL - 1} that need it (lane / kCh selects the row), and is skipped if there
   // are none (back-to-back global-to-LDS loads issue slowly, so only the needed ones go out).
   auto patch = [&](lds_t* buf, gmem_t* live, gmem_t* cache, const uint32_t* off, int stage_in)
                    __attribute__((always_inline)) {
+    constexpr uint32_t kRowMask = (1u << kRPL) - 1u;
     const int st = __builtin_amdgcn_readfirstlane(stage_in);
     if (st == spC) {
       gmem_t* lb = uniform_ptr((const void*)(live + st * stage_bytes));
@@ -440,13 +483,15 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
       const uint32_t vm = (1u << nv) - 1u;
 #pragma unroll
       for (int j = 0; j < kLoads; ++j)
-        if ((vm >> (4 * j)) & 15u) dma16m(wdst(buf, j), lb, off[j], lane_quads((vm >> (4 * j)) & 15u));
+        if ((vm >> (kRPL * j)) & kRowMask)
+          dma16m(wdst(buf, j), lb, off[j], lane_rows<D>((vm >> (kRPL * j)) & kRowMask));
     }
     gmem_t* cb = uniform_ptr((const void*)(cache + st * stage_bytes));
     const uint32_t sc = seed_chunk(st);  // seeds lie below L
 #pragma unroll
     for (int j = 0; j < kLoads; ++j)
-      if ((sc >> (4 * j)) & 15u) dma16m(wdst(buf, j), cb, off[j], lane_quads((sc >> (4 * j)) & 15u));
+      if ((sc >> (kRPL * j)) & kRowMask)
+        dma16m(wdst(buf, j), cb, off[j], lane_rows<D>((sc >> (kRPL * j)) & kRowMask));
   };
 
   // ---- diagonal set-up --------------------------------------------------------------------
@@ -485,15 +530,18 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
       const int r = 64 * qb + 32 * (t ^ kh) + l32;
-      asm volatile("ds_read_b128 %0, %1" : "=a"(qa[t][ks]) : "v"(lds_u32v((lds_t*)sQ + k_off(r, 2 * ks + hl))));
+      if constexpr (D == 128)
+        asm volatile("ds_read_b128 %0, %1" : "=a"(qa[t][ks]) : "v"(lds_u32v((lds_t*)sQ + k_off<D>(r, 2 * ks + hl))));
+      else
+        qa[t][ks] = __builtin_bit_cast(bf16x8, lds_read16((lds_t*)sQ + k_off<D>(r, 2 * ks + hl)));
     }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the Q reads above (not tracked by the compiler)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the Q reads above (D = 128: not tracked by the compiler)
   COVER_TSTAMP(4);
 
   // ---- per-lane LDS read addresses (relative to a stage buffer) ---------------------------
   uint32_t kaddr[kKS];
 #pragma unroll
-  for (int ks = 0; ks < kKS; ++ks) kaddr[ks] = k_off(kh * 32 + l32, 2 * ks + hl);
+  for (int ks = 0; ks < kKS; ++ks) kaddr[ks] = k_off<D>(kh * 32 + l32, 2 * ks + hl);
   // A operand of O^T += V^T P^T for keys kh*32 + 16 kk + {0..3, 8..11} + 4 (G / 2), d-block
   // db: lane (G = lane / 16, i = lane % 16) reads V[row][db*32 + 16 (G % 2) + 4 (i % 4) .. +3]
   // with row = kh*32 + 16 kk + 4 (G / 2) + i / 4 (+8 for the upper half); the same key order
@@ -504,7 +552,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
     const int G = lane >> 4, ii = lane & 15;
     const int row = kh * 32 + 4 * (G >> 1) + (ii >> 2);
 #pragma unroll
-    for (int db = 0; db < kDB; ++db) vaddr[db] = v_elem(row, db * 32 + 16 * (G & 1) + 4 * (ii & 3));
+    for (int db = 0; db < kDB; ++db) vaddr[db] = v_elem<D>(row, db * 32 + 16 * (G & 1) + 4 * (ii & 3));
   }
 
   // ---- compute pieces ----------------------------------------------------------------------
@@ -513,16 +561,16 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
     constexpr int A = decltype(ahead)::value;
     bf16x8 a[kKS];
 #pragma unroll
-    for (int ks = 0; ks < A; ++ks) a[ks] = __builtin_bit_cast(bf16x8, lds_read16(kb + kaddr[ks]));
+    for (int ks = 0; ks < A && ks < kKS; ++ks) a[ks] = __builtin_bit_cast(bf16x8, lds_read16(kb + kaddr[ks]));
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
       if (ks + A < kKS) a[ks + A] = __builtin_bit_cast(bf16x8, lds_read16(kb + kaddr[ks + A]));
       if (ks == 0) {
-        mfma_first(s[0], a[0], qa[0][ks]);
-        mfma_first(s[1], a[0], qa[1][ks]);
+        mfma_first<D>(s[0], a[0], qa[0][ks]);
+        mfma_first<D>(s[1], a[0], qa[1][ks]);
       } else {
-        mfma_v(s[0], a[ks], qa[0][ks]);
-        mfma_v(s[1], a[ks], qa[1][ks]);
+        mfma_v<D>(s[0], a[ks], qa[0][ks]);
+        mfma_v<D>(s[1], a[ks], qa[1][ks]);
       }
     }
   };
@@ -591,7 +639,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) valu_to_mfma(pk[t][kk]);
+      for (int kk = 0; kk < 2; ++kk) valu_to_mfma<D>(pk[t][kk]);
     bf16x8 va[2 * kDB];  // operand n: kk = n / kDB, db = n % kDB
     auto vread = [&](int n) __attribute__((always_inline)) {
       const lds_t* base = vb + vaddr[n % kDB] + (n / kDB) * 16 * kRow;
@@ -599,12 +647,12 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
           bf16x8, __builtin_shufflevector(v_tr(base), v_tr(base + 8 * kRow), 0, 1, 2, 3, 4, 5, 6, 7));
     };
 #pragma unroll
-    for (int n = 0; n < A; ++n) vread(n);
+    for (int n = 0; n < A && n < 2 * kDB; ++n) vread(n);
 #pragma unroll
     for (int n = 0; n < 2 * kDB; ++n) {
       if (n + A < 2 * kDB) vread(n + A);
-      mfma_a(o[0][n % kDB], va[n], pk[0][n / kDB]);
-      mfma_a(o[1][n % kDB], va[n], pk[1][n / kDB]);
+      mfma_a<D>(o[0][n % kDB], va[n], pk[0][n / kDB]);
+      mfma_a<D>(o[1][n % kDB], va[n], pk[1][n / kDB]);
     }
   };
 
@@ -634,18 +682,18 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
       if (ks == 0) {
-        mfma_first(sn[0], ka[0], qa[0][0]);
-        mfma_first(sn[1], ka[0], qa[1][0]);
+        mfma_first<D>(sn[0], ka[0], qa[0][0]);
+        mfma_first<D>(sn[1], ka[0], qa[1][0]);
       } else {
-        mfma_v(sn[0], ka[ks], qa[0][ks]);
-        mfma_v(sn[1], ka[ks], qa[1][ks]);
+        mfma_v<D>(sn[0], ka[ks], qa[0][ks]);
+        mfma_v<D>(sn[1], ka[ks], qa[1][ks]);
       }
       if (ks + 4 < kKS) ka[ks + 4] = __builtin_bit_cast(bf16x8, lds_read16(kb + kaddr[ks + 4]));
-      else vread(0, ks - 4);
+      else if (ks >= kKS - kDB) vread(0, ks - (kKS - kDB));
       if ((ks & 1) == 0) dma16s(wdst(kdst, ks >> 1), kg, offK[ks >> 1]);
-      // elements 2 ks, 2 ks + 1 of the order (t0 r0-7, t1 r0-7, t0 r8-15, t1 r8-15)
+      // 16 / kKS elements of the order (t0 r0-7, t1 r0-7, t0 r8-15, t1 r8-15) per k-step
 #pragma unroll
-      for (int u = 0; u < 2; ++u) expo(ks * 2 + u);
+      for (int u = 0; u < 16 / kKS; ++u) expo(ks * (16 / kKS) + u);
     }
     bf16x8 pk[2][2];
     auto cvt = [&](int kk) __attribute__((always_inline)) {
@@ -654,24 +702,24 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
         pk[t][kk] = kk == 0
             ? __builtin_convertvector(__builtin_shufflevector(pr[t], pr[t], 0, 1, 2, 3, 4, 5, 6, 7), bf16x8)
             : __builtin_convertvector(__builtin_shufflevector(pr[t], pr[t], 8, 9, 10, 11, 12, 13, 14, 15), bf16x8);
-        valu_to_mfma(pk[t][kk]);
+        valu_to_mfma<D>(pk[t][kk]);
       }
     };
     cvt(0);
 #pragma unroll
     for (int db = 0; db < kDB; ++db) {
-      mfma_a(o[0][db], va[0][db], pk[0][0]);
-      mfma_a(o[1][db], va[0][db], pk[1][0]);
+      mfma_a<D>(o[0][db], va[0][db], pk[0][0]);
+      mfma_a<D>(o[1][db], va[0][db], pk[1][0]);
       vread(1, db);
       dma16s(wdst(vdst, db), vg, offV[db]);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) expo(16 + db * 4 + u);
+      for (int u = 0; u < 16 / kDB; ++u) expo(16 + db * (16 / kDB) + u);
     }
     cvt(1);
 #pragma unroll
     for (int db = 0; db < kDB; ++db) {
-      mfma_a(o[0][db], va[1][db], pk[0][1]);
-      mfma_a(o[1][db], va[1][db], pk[1][1]);
+      mfma_a<D>(o[0][db], va[1][db], pk[0][1]);
+      mfma_a<D>(o[1][db], va[1][db], pk[1][1]);
     }
     return rowsums(pk);
   };
@@ -679,7 +727,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
   // ---- prologue compute: S(0) and the reference row maxima --------------------------------
   f32x16 sA[2], sB[2];
   qk(kbuf(0), sA, IC<4>{});
-  mfma_drain();
+  mfma_drain<D>();
   if (is_special(0)) special_fix(0, sA);
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -736,10 +784,10 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
   };
   float s_live = 0.0f;
   // The seed rows among the finished tile's queries (its 32 positions are bitmap word qd0 / 32):
-  // their live key and value rows go to this wave's 8 KiB of the Q area (free from the first
-  // step until the output tile is staged there) by global-to-LDS loads, four rows per load,
-  // issued with the last step; slot k holds the k-th seed row (key at 256 k, value at 4096 +
-  // 256 k).  A tile with more than 16 seed rows (or a sequence without steps) loads the rows
+  // their live key and value rows go to this wave's 32 rows of the Q area (free from the first
+  // step until the output tile is staged there) by global-to-LDS loads, kRPL rows per
+  // load, issued with the last step; slot k holds the k-th seed row (key at row k, value at row
+  // 16 + k).  A tile with more than 16 seed rows (or a sequence without steps) loads the rows
   // of all its queries into registers instead.
   const uint32_t dmask = block_seeded ? bits[qd0 >> 5] : 0u;
   const bool diag_lds = __builtin_popcount(dmask) <= 16 && last > 0;
@@ -749,17 +797,17 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
     for (int u = 0; msk; ++u) {
       int r = -1;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < kRPL; ++g) {
         if (msk) {
           const int b = __builtin_ctz(msk);
           msk &= msk - 1;
-          if ((lane >> 4) == g) r = b;
+          if (lane / kCh == g) r = b;
         }
       }
       if (r >= 0) {
-        const int64_t src = (int64_t)(qd0 + r) * row_bytes + ((lane & 15) << 4);
+        const int64_t src = (int64_t)(qd0 + r) * row_bytes + ((lane % kCh) << 4);
         dma16(lds_u32(dgA + u * 1024), klb + src);
-        dma16(lds_u32(dgA + 4096 + u * 1024), vlb + src);
+        dma16(lds_u32(dgA + 16 * kRow + u * 1024), vlb + src);
       }
     }
   };
@@ -770,7 +818,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
     for (int ks = 0; ks < kKS; ++ks) dkr[ks] = lds_read16(dgA + dslot * kRow + (2 * ks + hl) * 16);
 #pragma unroll
     for (int c = 0; c < kDB * 4; ++c)
-      dvr[c] = qd_seed ? *(const __attribute__((address_space(3))) u32x2*)(dgA + 4096 + dslot * kRow + 16 * c + 8 * hl)
+      dvr[c] = qd_seed ? *(const __attribute__((address_space(3))) u32x2*)(dgA + 16 * kRow + dslot * kRow + 16 * c + 8 * hl)
                        : (u32x2){0u, 0u};
   };
   uint64_t win = flags_at(0);  // the row-by-row flags of stages (i & ~31) + 0 .. 63
@@ -801,7 +849,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
     if (__builtin_expect(block_seeded && i == last - 1, 0)) {
       if (diag_lds) {
         issue_diag();
-      } else {
+      } else if constexpr (D == 128) {  // (D = 64 has no registers to hold them across the step)
         load_diag_k();
         load_diag_v();
       }
@@ -830,7 +878,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
     // of the previous step (stages past the end) and the diagonal rows issued before them may
     // stay in flight (loads complete in order).  Every load has landed before the buffers are
     // reused after this block.
-    if (block_seeded && last == 0) {  // (no steps: the diagonal rows are loaded here)
+    if (block_seeded && (last == 0 || (D == 64 && !diag_lds))) {  // the diagonal rows are loaded here
       load_diag_k();
       load_diag_v();
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -858,7 +906,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
 
   // ---- exact pass (only if some row's scores outgrew its first-stage maximum by 2^24) ----
   if (sbad) {
-    mfma_drain();
+    mfma_drain<D>();
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       m[t] = kInitMax;
@@ -874,7 +922,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
       __syncthreads();
       f32x16 s[2];
       qk(kbuf(0), s, IC<0>{});
-      mfma_drain();
+      mfma_drain<D>();
       if (is_special(it)) special_fix(it, s);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -889,12 +937,12 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
       bf16x8 pk[2][2];
       (void)softmax(s, pk, m);
       pv(vbuf(0), pk, IC<0>{});
-      mfma_drain();
+      mfma_drain<D>();
     }
     __syncthreads();
   }
 
-  mfma_drain();
+  mfma_drain<D>();
   // ---- merge the two key halves, add the live diagonal term, normalise, store --------------
   // Wave w finishes its tile 0; its tile 1 goes to the partner w ^ 2 (for which it is tile 0)
   // through LDS (16 KiB per wave: buffers V0, V1, V2, K2 are free now), with that tile's m and
@@ -965,7 +1013,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
   lds_t* const tile = (lds_t*)sQ + wave * (32 * kRow);
 #pragma unroll
   for (int n = 0; n < kDB * 4; ++n)
-    *(__attribute__((address_space(3))) bf16x4*)(tile + k_off(l32, n) + hl * 8) = outv[n];
+    *(__attribute__((address_space(3))) bf16x4*)(tile + k_off<D>(l32, n) + hl * 8) = outv[n];
   constexpr int CPR = kRow / 16;       // 16-byte chunks per row
   constexpr int NRD = 32 * CPR / 64;   // reads (and stores) per lane
   __bf16* const obase = p.out + b * p.q_sb + h * p.q_sh;
@@ -973,7 +1021,7 @@ __global__ __launch_bounds__(kThreads, 1) void cover_attn_w4_kernel(const Params
 #pragma unroll
   for (int it = 0; it < NRD; ++it) {
     const int idx = it * 64 + lane, row = idx / CPR, ch = idx % CPR;
-    ov[it] = *(const __attribute__((address_space(3))) u32x4*)(tile + k_off(row, ch));
+    ov[it] = *(const __attribute__((address_space(3))) u32x4*)(tile + k_off<D>(row, ch));
   }
   if (qd0 + 32 <= L) {
 #pragma unroll
@@ -1008,7 +1056,7 @@ extern "C" int cover_attn_timing_read(uint64_t* host, int64_t n) {
 }
 #endif
 
-hipError_t launch_attn_bf16_w4(const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream) {
   Params4 p;
   p.q = (const __bf16*)a.q;
   p.kl = (const __bf16*)a.k_live;
@@ -1027,8 +1075,9 @@ hipError_t launch_attn_bf16_w4(const AttnArgs& a, hipStream_t stream) {
   p.c2 = a.scale * 1.44269504088896341f;
   p.q_sb = a.q_sb; p.q_sh = a.q_sh; p.q_sl = a.q_sl;
   p.kv_sb = a.kv_sb; p.kv_sh = a.kv_sh; p.kv_sl = a.kv_sl;
-  if (nwg > 0x7fffffff || a.d != kD) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(cover_attn_w4_kernel, dim3((unsigned)nwg), dim3(kThreads), 0, stream, p);
+  if (nwg > 0x7fffffff || (a.d != 128 && a.d != 64)) return hipErrorInvalidConfiguration;
+  if (a.d == 128) hipLaunchKernelGGL(cover_attn_w4_kernel<128>, dim3((unsigned)nwg), dim3(kThreads), 0, stream, p);
+  else hipLaunchKernelGGL(cover_attn_w4_kernel<64>, dim3((unsigned)nwg), dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
 

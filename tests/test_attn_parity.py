@@ -131,6 +131,28 @@ def test_bf16_every_position_a_seed(d):
     check_attn(out, lse, ref, lref, torch.bfloat16, "all-seeds")
 
 
+@pytest.mark.parametrize("L,n,layout,late", [(32, 17, "head", False), (64, 40, "token", False), (65, 3, "head", False),
+                                             (128, 30, "token", False), (193, 100, "head", False),
+                                             (449, 25, "token", True), (577, 200, "head", True)])
+def test_bf16_d64_edges(L, n, layout, late):
+    """Head size 64: whole and ragged stages and query tiles, one to ten stages, tiles with more
+    and fewer than 16 seed rows, token-major strides, and (late) scores that outgrow the first
+    stage's by more than 2^24, so the tile is computed again with per-stage rescaling."""
+    announce(f"bf16 d64 L{L} seeds{n} {layout} late {late}")
+    a = _custom(L, 2, 4, 2, L, 64, n)
+    if late:
+        for k in ("k_live", "k_cache"):
+            a[k][:, :, 3 * L // 4:] *= 40.0
+    if layout == "token":
+        for k in ("q", "k_live", "v_live", "k_cache", "v_cache"):
+            a[k] = a[k].transpose(1, 2).contiguous().transpose(1, 2)
+    out, lse = _run(a)
+    ref, lref = _oracle(a)
+    if late:  # scores of some hundreds: bf16 rounds nothing in them, fp32 sums to 2^-24 of their size
+        assert np.abs(lref).max() > 30
+    check_attn(out, lse, ref, lref, torch.bfloat16, f"L{L}")
+
+
 def test_zero_seeds_and_no_seed_arrays():
     announce("bf16 zero seeds / max_seeds 0")
     a = _custom(5, 1, 4, 2, 200, 128, 6)
