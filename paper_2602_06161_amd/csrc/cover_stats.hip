@@ -243,6 +243,12 @@ __device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// 16 values, in a tree of depth 4 (a chain of 16 rounds the larger partial sums 16 times)
+__device__ __forceinline__ float tree_sum(const f32x4* w) {
+  const f32x4 a = (w[0] + w[1]) + (w[2] + w[3]);
+  return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
 constexpr int kStatWaves = 8;
 constexpr int kStatThreads = 64 * kStatWaves;
 constexpr int kSegs = COVER_STATS_MAX_LR / 64;              // 64-position segments of the region
@@ -270,7 +276,12 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
   const __bf16* qbh = p.q + b * p.q_sb + h * p.q_sh + p.r0 * p.q_sl;  // region position 0
   const int64_t kvo = b * p.kv_sb + g * p.kv_sh + p.r0 * p.kv_sl;
   const float* lrow = p.lse + ((int64_t)b * p.Hq + h) * p.L + p.r0;
-  const float c2 = p.scale * kLog2e;
+  // (the difference before the change of base: rounding lse log2 e first costs up to 2^-24 of
+  // its size in every weight of a query)
+  const float scale = p.scale;
+  auto weight = [=](float s, float lse) __attribute__((always_inline)) -> float {
+    return __builtin_amdgcn_exp2f(__builtin_fmaf(s, scale, -lse) * kLog2e);
+  };
 
   // ---- the seed count and list, membership and lse of every position: one round trip --------
   const int ns_raw = p.max_seeds > 0 ? p.n_seed[b] : 0;
@@ -327,7 +338,7 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
       if ((um >> lane) & 1) {
         const int at = base_m[m] + __builtin_popcountll(um & below);
         list_m[at] = (uint16_t)(s * 64 + lane);
-        lse_m[at] = ls[m] * kLog2e;
+        lse_m[at] = ls[m];
       }
       if ((ud >> lane) & 1) list_d[base_d[m] + __builtin_popcountll(ud & below)] = (uint16_t)(s * 64 + lane);
     }
@@ -424,6 +435,7 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
       f32x16 s[NK];
       product(s);
       if (__builtin_amdgcn_readfirstlane(any_own) != 0) diagonal(s, list_m, n_m, t);
+      f32x4 w4[NK][4];  // a tile's 16 weights are added as a tree, then to the running sum
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const f32x4 lq = *(const f32x4*)(lse_m + 32 * t + 8 * q + 4 * hl);
@@ -431,8 +443,10 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
         for (int n = 0; n < NK; ++n)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            din[n] += __builtin_amdgcn_exp2f(__builtin_fmaf(s[n][4 * q + e], c2, -lq[e]));
+            w4[n][q][e] = weight(s[n][4 * q + e], lq[e]);
       }
+#pragma unroll
+      for (int n = 0; n < NK; ++n) din[n] += tree_sum(w4[n]);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) fa[ks] = fn[ks];
     }
@@ -444,7 +458,7 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
 #pragma unroll
       for (int n = 0; n < NK; ++n) {
         load_q(fb[n], jt[n]);
-        lq[n] = lrow[jt[n]] * kLog2e;
+        lq[n] = lrow[jt[n]];
       }
       for (int t = d_first; t < d_tiles; t += p.wpk) {
         if (t + p.wpk < d_tiles) load_k(fn, listed(list_d, n_d, t + p.wpk));
@@ -453,12 +467,15 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
         if (__builtin_amdgcn_readfirstlane(any_own) != 0) diagonal(s, list_d, n_d, t);
         const int lim = n_d - 32 * t - 4 * hl;  // rows past the list's end have no weight
 #pragma unroll
-        for (int n = 0; n < NK; ++n)
+        for (int n = 0; n < NK; ++n) {
+          f32x4 w4[4];
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[n][r], c2, -lq[n]));
-            dout[n] += 8 * (r >> 2) + (r & 3) < lim ? w : 0.0f;
+            const float w = weight(s[n][r], lq[n]);
+            w4[r >> 2][r & 3] = 8 * (r >> 2) + (r & 3) < lim ? w : 0.0f;
           }
+          dout[n] += tree_sum(w4);
+        }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) fa[ks] = fn[ks];
       }
