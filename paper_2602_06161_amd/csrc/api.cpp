@@ -80,6 +80,18 @@ cover_status cover_attn_fwd(const void* q, const void* k_live, const void* v_liv
     if (e != hipSuccess) return COVER_ERR_HIP;
   }
   if (D.dtype != COVER_BF16) return hip_status(cover::launch_attn_f32(a, stream));
+  if (cover::attn_small(a)) {
+    // every query row as one block of the block kernel's single launch
+    cover::RectArgs r;
+    r.q = a.q; r.k_live = a.k_live; r.v_live = a.v_live; r.k_cache = a.k_cache; r.v_cache = a.v_cache;
+    r.seed_idx = a.seed_idx; r.n_seed = a.n_seed; r.out = a.out; r.lse = a.lse; r.workspace = nullptr;
+    r.B = a.B; r.Hq = a.Hq; r.Hkv = a.Hkv; r.L = a.L; r.d = a.d; r.max_seeds = a.max_seeds;
+    r.q_off = 0; r.Lq = a.L; r.n_split = 1;
+    r.scale = a.scale;
+    r.q_sb = a.q_sb; r.q_sh = a.q_sh; r.q_sl = a.q_sl;
+    r.kv_sb = a.kv_sb; r.kv_sh = a.kv_sh; r.kv_sl = a.kv_sl;
+    return hip_status(cover::launch_attn_rect(r, stream));
+  }
   return hip_status(cover::launch_attn_bf16(a, stream));
 }
 
@@ -302,7 +314,7 @@ cover_status cover_attn_rect(const void* q, const void* k_live, const void* v_li
   a.n_seed = D.max_seeds > 0 ? n_seed : nullptr;
   a.out = out; a.lse = lse; a.workspace = n_split > 1 ? workspace : nullptr;
   a.B = D.B; a.Hq = D.Hq; a.Hkv = D.Hkv; a.L = D.L; a.max_seeds = D.max_seeds;
-  a.q_off = q_off; a.Lq = Lq; a.n_split = n_split;
+  a.d = D.d; a.q_off = q_off; a.Lq = Lq; a.n_split = n_split;
   a.scale = D.scale > 0.0f ? D.scale : 1.0f / sqrtf((float)D.d);
   a.q_sb = D.q_sb; a.q_sh = D.q_sh; a.q_sl = D.q_sl;
   a.kv_sb = D.kv_sb; a.kv_sh = D.kv_sh; a.kv_sl = D.kv_sl;

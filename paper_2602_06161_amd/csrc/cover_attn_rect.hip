@@ -1,6 +1,7 @@
 // COVER attention for a block of queries against the whole sequence (the prefix-cache
 // decoding combined with COVER in Sec. 6.6: only the current block's rows are recomputed; the
-// prompt's keys and values come from the caller's cache), bf16, head size 128, on gfx950.
+// prompt's keys and values come from the caller's cache), bf16, head size 128, on gfx950; and
+// small square calls (at most 256 tiles of 32 query rows), also at head size 64.
 //
 // Per query row i at absolute position p = q_off + r the result is the row p of the square
 // COVER attention (Sec. 5.1): keys and values of seed positions come from the cache, every
@@ -39,8 +40,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_t;
 typedef __attribute__((address_space(1))) const char gmem_t;
 
-constexpr int kD = 128;
-constexpr int kRow = 2 * kD;            // bytes per K/V row
+constexpr int kD = 128;                 // head size of the key splits' records
 constexpr int kStage = 32;              // keys per stage
 constexpr int kMaxWords = COVER_MAX_L / 32;
 constexpr float kInit = -1.0e30f;       // finite "nothing seen yet" max
@@ -65,12 +65,20 @@ struct RectParams {
   int first_wg, wide;
 };
 
-// LDS layouts: K rows with the 16-byte chunk index XOR-ed by row % 16 (a b128 operand read of
-// 32 rows covers all banks); V rows with the chunk index XOR-ed by 4 (row % 4) (a transposing
-// read of 8 rows x 64 bytes covers every bank twice).
-__device__ __forceinline__ uint32_t k_off(int row, int c) { return row * kRow + ((c ^ (row & 15)) << 4); }
-__device__ __forceinline__ uint32_t v_chunk(int row, int c) { return row * kRow + ((c ^ ((row & 3) << 2)) << 4); }
-__device__ __forceinline__ uint32_t v_elem(int row, int col) { return v_chunk(row, col >> 3) + ((col & 7) << 1); }
+// LDS layouts: K rows with the 16-byte chunk index XOR-ed by row % 16 (head size 64, two rows
+// per 256-byte window: row / 2 % 8), so that a b128 operand read of 32 rows covers all banks; V
+// rows with the chunk index XOR-ed by 4 (row % 4) (2 (row % 4)), so that a transposing read of 8
+// rows x 64 bytes covers every bank twice.
+template <int D>
+__device__ __forceinline__ int k_swz(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+template <int D>
+__device__ __forceinline__ int v_swz(int row) { return (row & 3) << (D == 128 ? 2 : 1); }
+template <int D>
+__device__ __forceinline__ uint32_t k_off(int row, int c) { return row * (2 * D) + ((c ^ k_swz<D>(row)) << 4); }
+template <int D>
+__device__ __forceinline__ uint32_t v_elem(int row, int col) {
+  return row * (2 * D) + (((col >> 3) ^ v_swz<D>(row)) << 4) + ((col & 7) << 1);
+}
 
 // max / sum of x over a query row's lane pair (lanes l and l ^ 32), on the VALU: the swap
 // leaves one copy of each lane's own value and one of its partner's in the two results
@@ -153,7 +161,6 @@ __global__ __launch_bounds__(256) void cover_attn_rect_merge_kernel(const RectPa
 // ---------------------------------------------------------------------------------------
 constexpr int kTW = 8;             // waves per workgroup
 constexpr int kTQ = 32;            // queries per workgroup
-constexpr int kSB = kStage * kRow; // bytes of one stage of K (or V)
 constexpr int kTSeeds = 64 * kTW;  // seed positions fetched into LDS (the rest: plain loads)
 constexpr float kLazyT = 8.0f;
 
@@ -186,11 +193,19 @@ __device__ __forceinline__ void dma4(uint32_t lds, gmem_t* addr) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
                :: "s"(lds), "v"((uint64_t)addr) : "memory", "m0");
 }
-// lanes 16 k .. 16 k + 15 for each set bit k of a 4-bit value
-__device__ __forceinline__ uint64_t lane_quads(uint32_t n) {
-  const uint64_t m = (uint64_t)(n & 1u) | ((uint64_t)(n & 2u) << 15) | ((uint64_t)(n & 4u) << 30) |
-                     ((uint64_t)(n & 8u) << 45);
-  return (m << 16) - m;
+// the lanes that load row k, for each set bit k: 16 k .. 16 k + 15 of 4 rows (head size 128), or
+// 8 k .. 8 k + 7 of 8 rows (64; the product puts bit k of a nibble at 8 k)
+template <int D>
+__device__ __forceinline__ uint64_t lane_rows(uint32_t n) {
+  if constexpr (D == 128) {
+    const uint64_t m = (uint64_t)(n & 1u) | ((uint64_t)(n & 2u) << 15) | ((uint64_t)(n & 4u) << 30) |
+                       ((uint64_t)(n & 8u) << 45);
+    return (m << 16) - m;
+  } else {
+    const uint64_t m = (uint64_t)(((n & 15u) * 0x00204081u) & 0x01010101u) |
+                       ((uint64_t)(((n >> 4) * 0x00204081u) & 0x01010101u) << 32);
+    return (m << 8) - m;
+  }
 }
 __device__ __forceinline__ gmem_t* uniform_ptr(const void* ptr) {
   const uint64_t v = (uint64_t)ptr;
@@ -220,16 +235,26 @@ __device__ uint64_t g_rect_times[kTimeWG * kTW * kTimeSlots];
 #endif
 
 // SPLIT: key splits (records for the merge kernel); otherwise the whole of a row's keys
-template <bool SPLIT>
+// (head size 128 only)
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const RectParams p) {
-  // per wave: a K slot and a V slot (at the end: its partial O, 32 rows of 128 fp32);
-  // the tile's Q; the seed bitmap of the sequence; the seed list; the partial maxima and sums
+  constexpr int kRow = 2 * D;              // bytes per K/V/Q row
+  constexpr int kCh = D / 8;               // 16-byte chunks per row
+  constexpr int kRPL = 1024 / kRow;        // rows per 1-KiB load
+  constexpr int kNL = kStage / kRPL;       // loads per stage of K (or V)
+  constexpr int kSB = kStage * kRow;       // bytes of one stage of K (or V)
+  constexpr uint32_t kRowMask = (1u << kRPL) - 1u;
+  // per wave: a K slot and a V slot (at the end: its partial O, 32 rows of D fp32);
+  // the tile's Q; the seed bitmap of the sequence; the seed list, and later in its place the
+  // partial maxima and sums
   __shared__ __attribute__((aligned(1024))) char sKV[kTW][2][kSB];
   __shared__ __attribute__((aligned(1024))) char sQ[kTQ * kRow];
   __shared__ uint32_t bits[kMaxWords];
   __shared__ __attribute__((aligned(16))) int32_t sSeeds[kTSeeds];
   __shared__ __attribute__((aligned(16))) int32_t sNs[4];
-  __shared__ float sM[kTW][kTQ], sL[kTW][kTQ];
+  static_assert(2 * kTW * kTQ <= kTSeeds, "the partial maxima and sums fit the seed list's place");
+  float (*const sM)[kTQ] = (float(*)[kTQ])sSeeds;
+  float (*const sL)[kTQ] = sM + kTW;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -266,16 +291,16 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
   const int nW = (L + 31) >> 5;
   for (int w = tid; w < nW; w += 64 * kTW) bits[w] = 0u;
 
-  // load geometry: load j of a stage covers stage rows 4 j + lane / 16 at physical chunk
-  // lane % 16, i.e. LDS byte 1024 j + 16 lane of the slot; the source chunk is the one the
-  // slot's swizzle puts there (K: chunk ^ row % 16; V: chunk ^ 4 (row % 4))
+  // load geometry: load j of a stage covers stage rows kRPL j + lane / kCh at physical chunk
+  // lane % kCh, i.e. LDS byte 1024 j + 16 lane of the slot; the source chunk is the one the
+  // slot's swizzle puts there (k_swz, v_swz)
   const int64_t row_bytes = p.kv_sl * 2, stage_bytes = kStage * row_bytes;
-  uint32_t offK[8], offV[8];
+  uint32_t offK[kNL], offV[kNL];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int row = 4 * j + (lane >> 4), pc = lane & 15;
-    offK[j] = (uint32_t)(row * row_bytes) + ((pc ^ (row & 15)) << 4);
-    offV[j] = (uint32_t)(row * row_bytes) + ((pc ^ ((row & 3) << 2)) << 4);
+  for (int j = 0; j < kNL; ++j) {
+    const int row = kRPL * j + lane / kCh, pc = lane % kCh;
+    offK[j] = (uint32_t)(row * row_bytes) + ((pc ^ k_swz<D>(row)) << 4);
+    offV[j] = (uint32_t)(row * row_bytes) + ((pc ^ v_swz<D>(row)) << 4);
   }
   const int64_t kvoff = b * p.kv_sb + g * p.kv_sh;
   const char* const klc = (const char*)(p.kl + kvoff);
@@ -289,8 +314,8 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
                       uint32_t seeds) __attribute__((always_inline)) {
     if (st == ragged || seeds != 0u || (SPLIT && p.wide)) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int row = 4 * j + (lane >> 4);
+      for (int j = 0; j < kNL; ++j) {
+        const int row = kRPL * j + lane / kCh;
         const int key = min(st * kStage + row, L - 1);
         const char* src = ((seeds >> row) & 1u) ? cache : live;
         dma16(slot + 1024 * j, (gmem_t*)(src + key * row_bytes + (off[j] - (uint32_t)(row * row_bytes))));
@@ -298,7 +323,7 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     } else {
       gmem_t* base = uniform_ptr(live + st * stage_bytes);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) dma16s(slot + 1024 * j, base, off[j]);
+      for (int j = 0; j < kNL; ++j) dma16s(slot + 1024 * j, base, off[j]);
     }
   };
   auto seed_word = [&](int st) __attribute__((always_inline)) -> uint32_t {
@@ -317,9 +342,9 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     }
     gmem_t* base = uniform_ptr(cache + st * stage_bytes);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t nib = (w >> (4 * j)) & 15u;
-      if (nib) dma16m(slot + 1024 * j, base, off[j], lane_quads(nib));
+    for (int j = 0; j < kNL; ++j) {
+      const uint32_t rows = (w >> (kRPL * j)) & kRowMask;
+      if (rows) dma16m(slot + 1024 * j, base, off[j], lane_rows<D>(rows));
     }
   };
 
@@ -331,15 +356,15 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     if (e < p.max_seeds) dma4(lds_addr((const char*)sSeeds + 256 * wave), (gmem_t*)(p.seed_idx + sbase + e));
   }
   const __bf16* qbase = p.q + b * p.q_sb + h * p.q_sh;
-  {
-    const int row = 4 * wave + (lane >> 4), pc = lane & 15;
+  if (kTQ / kRPL == kTW || wave < kTQ / kRPL) {
+    const int row = kRPL * wave + lane / kCh, pc = lane % kCh;
     const int qi = min(qt * kTQ + row, p.Lq - 1);
-    dma16(lds_addr(sQ + 1024 * wave), (gmem_t*)((const char*)(qbase + (int64_t)qi * p.q_sl) + ((pc ^ (row & 15)) << 4)));
+    dma16(lds_addr(sQ + 1024 * wave), (gmem_t*)((const char*)(qbase + (int64_t)qi * p.q_sl) + ((pc ^ k_swz<D>(row)) << 4)));
   }
   if (s0 < s1) {
     ld_stage(slotK, klc, kcc, offK, s0, 0u);
     ld_stage(slotV, vlc, vcc, offV, s0, 0u);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));  // the seed list and Q have landed
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kNL));  // the seed list and Q have landed
   } else {
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   }
@@ -366,41 +391,43 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
   }
 
   // Q fragments (B operand of S^T = K Q^T): query l32, d-chunk 2 ks + hl
-  bf16x8 qreg[kD / 16];
+  bf16x8 qreg[D / 16];
 #pragma unroll
-  for (int ks = 0; ks < kD / 16; ++ks)
-    qreg[ks] = *(const __attribute__((address_space(3))) bf16x8*)((const lds_t*)sQ + k_off(l32, 2 * ks + hl));
+  for (int ks = 0; ks < D / 16; ++ks)
+    qreg[ks] = *(const __attribute__((address_space(3))) bf16x8*)((const lds_t*)sQ + k_off<D>(l32, 2 * ks + hl));
   const int qrow = min(qt * kTQ + l32, p.Lq - 1);
   const int pos = p.q_off + qrow;
   const bool row_seed = is_seed(pos);
 
   // the live key and value rows of the seed rows this wave finishes: lane group fq = lane / 16
-  // takes query kFin wave + fq, dims 8 (lane % 16) .. + 7, requested now and used in the merge
-  constexpr int kFin = kTQ / kTW;
+  // takes query kFin wave + fq, dims kE (lane % 16) .. + kE - 1, requested now and used in the merge
+  constexpr int kFin = kTQ / kTW, kE = D / 16;
+  typedef uint32_t raw_t __attribute__((ext_vector_type(kE / 2)));  // kE bf16 values
+  typedef __bf16 out_t __attribute__((ext_vector_type(kE)));
   const int fq = lane >> 4, fj = lane & 15;
   const int qfin = qt * kTQ + kFin * wave + fq;
   const bool fin_ok = qfin < p.Lq;
   // (with key splits the diagonal term belongs to the split that holds the position)
   const int fstage = (p.q_off + qfin) / kStage;
   const bool fseed = fin_ok && (!SPLIT || (fstage >= sb && fstage < sb + nst)) && is_seed(p.q_off + qfin);
-  u32x4 kd = {0u, 0u, 0u, 0u}, vd = {0u, 0u, 0u, 0u};
+  raw_t kd = {}, vd = {};
   if (fseed) {
-    const int64_t ro = kvoff + (int64_t)(p.q_off + qfin) * p.kv_sl + 8 * fj;
-    kd = *(const u32x4*)(p.kl + ro);
-    vd = *(const u32x4*)(p.vl + ro);
+    const int64_t ro = kvoff + (int64_t)(p.q_off + qfin) * p.kv_sl + kE * fj;
+    kd = *(const raw_t*)(p.kl + ro);
+    vd = *(const raw_t*)(p.vl + ro);
   }
 
   // V^T operand addresses (as in the split kernel)
-  uint32_t vaddr[kD / 32];
+  uint32_t vaddr[D / 32];
   {
     const int G = lane >> 4, ii = lane & 15;
     const int row = 4 * (G >> 1) + (ii >> 2);
 #pragma unroll
-    for (int db = 0; db < kD / 32; ++db) vaddr[db] = v_elem(row, db * 32 + 16 * (G & 1) + 4 * (ii & 3));
+    for (int db = 0; db < D / 32; ++db) vaddr[db] = v_elem<D>(row, db * 32 + 16 * (G & 1) + 4 * (ii & 3));
   }
-  f32x16 o[kD / 32];
+  f32x16 o[D / 32];
 #pragma unroll
-  for (int db = 0; db < kD / 32; ++db)
+  for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
   float m = kInit, l = 0.0f;
@@ -409,23 +436,23 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
 
   for (int st = s0; st < s1; ++st) {
     const bool more = st + 1 < s1;
-    // K(st) has landed: younger are V(st)'s 8 loads; at the first stage everything is waited
+    // K(st) has landed: younger are V(st)'s kNL loads; at the first stage everything is waited
     // for (the patches of the prologue are counted nowhere)
     if (st == s0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(kNL));
     if (st == s0) RECT_TSTAMP(3);
     if (st - s0 < 16) RECT_TSTAMP(4 + st - s0);
-    bf16x8 ka[kD / 16];
+    bf16x8 ka[D / 16];
 #pragma unroll
-    for (int ks = 0; ks < kD / 16; ++ks)
-      ka[ks] = *(const __attribute__((address_space(3))) bf16x8*)(kb + k_off(l32, 2 * ks + hl));
+    for (int ks = 0; ks < D / 16; ++ks)
+      ka[ks] = *(const __attribute__((address_space(3))) bf16x8*)(kb + k_off<D>(l32, 2 * ks + hl));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K slot is read: refill it
     if (more) ld_stage(slotK, klc, kcc, offK, st + 1, seed_word(st + 1));
     f32x16 sc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
 #pragma unroll
-    for (int ks = 0; ks < kD / 16; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qreg[ks], sc, 0, 0, 0);
+    for (int ks = 0; ks < D / 16; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qreg[ks], sc, 0, 0, 0);
     // register r holds key k0 + 8 (r / 4) + 4 hl + r % 4 of query qrow
     const int k0 = st * kStage;
     const bool edge = k0 + kStage > L;
@@ -455,7 +482,7 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
       const float alpha = __builtin_amdgcn_exp2f(m - mn);
       l *= alpha;
 #pragma unroll
-      for (int db = 0; db < kD / 32; ++db) o[db] *= alpha;
+      for (int db = 0; db < D / 32; ++db) o[db] *= alpha;
       m = mn;
     }
     bf16x8 pk[2];
@@ -467,14 +494,14 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
         l += pr;
         pk[kk][e] = (__bf16)pr;
       }
-    // V(st) has landed: younger are K(st + 1)'s 8 loads, if there is a stage st + 1
-    if (more) __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+    // V(st) has landed: younger are K(st + 1)'s kNL loads, if there is a stage st + 1
+    if (more) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kNL));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    bf16x8 va[2][kD / 32];
+    bf16x8 va[2][D / 32];
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int db = 0; db < kD / 32; ++db) {
+      for (int db = 0; db < D / 32; ++db) {
         const lds_t* base = vb + vaddr[db] + kk * 16 * kRow;
         va[kk][db] = __builtin_bit_cast(
             bf16x8, __builtin_shufflevector(v_tr(base), v_tr(base + 8 * kRow), 0, 1, 2, 3, 4, 5, 6, 7));
@@ -486,47 +513,50 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int db = 0; db < kD / 32; ++db)
+      for (int db = 0; db < D / 32; ++db)
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[kk][db], pk[kk], o[db], 0, 0, 0);
   }
 
   // ---- merge: every wave's (max, sum, O) through LDS ---------------------------------------
   // O goes to this wave's own slots (its loads have all landed and been read): row l32, 16-byte
-  // chunk c (dims 4 c .. 4 c + 3) at byte 512 l32 + 16 (c ^ l32)
+  // chunk c (dims 4 c .. 4 c + 3) at byte 4 D l32 + 16 (c ^ l32 % (D / 4))
   RECT_TSTAMP(20);
+  constexpr int kOM = D / 4 - 1;
   const float lt = pair_sum(l);
   if (hl == 0) {
     sM[wave][l32] = m;
     sL[wave][l32] = lt;
   }
   {
-    lds_t* const ob = (lds_t*)sKV[wave][0] + 512 * l32;
+    lds_t* const ob = (lds_t*)sKV[wave][0] + 4 * D * l32;
 #pragma unroll
-    for (int db = 0; db < kD / 32; ++db)
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
         const int c = 8 * db + 2 * gq + hl;
-        *(__attribute__((address_space(3))) f32x4*)(ob + ((c ^ l32) << 4)) =
+        *(__attribute__((address_space(3))) f32x4*)(ob + ((c ^ (l32 & kOM)) << 4)) =
             f32x4{o[db][4 * gq], o[db][4 * gq + 1], o[db][4 * gq + 2], o[db][4 * gq + 3]};
       }
   }
   __syncthreads();
   RECT_TSTAMP(21);
-  // wave w finishes queries kFin w + fq (lane group fq), lane dims 8 fj .. 8 fj + 7; every
+  // wave w finishes queries kFin w + fq (lane group fq), lane dims kE fj .. kE fj + kE - 1; every
   // LDS read of the merge is requested before the first is used
   {
     const int f = kFin * wave + fq;
     float mw[kTW], lw[kTW];
-    f32x4 ow[kTW][2];
+    f32x4 ow[kTW][kE / 4];
 #pragma unroll
     for (int w = 0; w < kTW; ++w) {
       mw[w] = sM[w][f];
       lw[w] = sL[w][f];
-      const lds_t* rb = (const lds_t*)sKV[w][0] + 512 * f;
-      ow[w][0] = *(const __attribute__((address_space(3))) f32x4*)(rb + (((2 * fj) ^ f) << 4));
-      ow[w][1] = *(const __attribute__((address_space(3))) f32x4*)(rb + (((2 * fj + 1) ^ f) << 4));
+      const lds_t* rb = (const lds_t*)sKV[w][0] + 4 * D * f;
+#pragma unroll
+      for (int u = 0; u < kE / 4; ++u)
+        ow[w][u] = *(const __attribute__((address_space(3))) f32x4*)(rb + (((kE / 4 * fj + u) ^ (f & kOM)) << 4));
     }
-    const u32x4 qv = *(const __attribute__((address_space(3))) u32x4*)((const lds_t*)sQ + k_off(f, fj));
+    const raw_t qv = *(const __attribute__((address_space(3))) raw_t*)(
+        (const lds_t*)sQ + k_off<D>(f, kE * fj / 8) + 2 * (kE * fj % 8));
     float M = kInit;
 #pragma unroll
     for (int w = 0; w < kTW; ++w) M = __builtin_fmaxf(M, mw[w]);
@@ -534,7 +564,7 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     // group's 16 lanes
     float dot = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < kE / 2; ++e) {
       dot = __builtin_fmaf(__uint_as_float(qv[e] << 16), __uint_as_float(kd[e] << 16), dot);
       dot = __builtin_fmaf(__uint_as_float(qv[e] & 0xffff0000u), __uint_as_float(kd[e] & 0xffff0000u), dot);
     }
@@ -542,24 +572,21 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     for (int off = 8; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
     const float t = dot * p.c2;
     if (fseed) M = __builtin_fmaxf(M, t);
-    float den = 0.0f, acc[8];
+    float den = 0.0f, acc[kE];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    for (int e = 0; e < kE; ++e) acc[e] = 0.0f;
 #pragma unroll
     for (int w = 0; w < kTW; ++w) {
       const float a = __builtin_amdgcn_exp2f(mw[w] - M);
       den = __builtin_fmaf(lw[w], a, den);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[e] = __builtin_fmaf(a, ow[w][0][e], acc[e]);
-        acc[4 + e] = __builtin_fmaf(a, ow[w][1][e], acc[4 + e]);
-      }
+      for (int e = 0; e < kE; ++e) acc[e] = __builtin_fmaf(a, ow[w][e >> 2][e & 3], acc[e]);
     }
     if (fseed) {
       const float pd = __builtin_amdgcn_exp2f(t - M);
       den += pd;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < kE / 2; ++e) {
         acc[2 * e] = __builtin_fmaf(pd, __uint_as_float(vd[e] << 16), acc[2 * e]);
         acc[2 * e + 1] = __builtin_fmaf(pd, __uint_as_float(vd[e] & 0xffff0000u), acc[2 * e + 1]);
       }
@@ -567,20 +594,20 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     if (SPLIT && fin_ok) {  // the split's record: O / sum in bf16, the max and the sum
       float* rec = p.ws + (((int64_t)bh * p.n_split + split) * p.Lq + qfin) * COVER_RECT_RECORD;
       const float inv = den > 0.0f ? 1.0f / den : 0.0f;
-      bf16x8 ob;
+      out_t ob;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(acc[e] * inv);
-      *(bf16x8*)((__bf16*)rec + 8 * fj) = ob;
+      for (int e = 0; e < kE; ++e) ob[e] = (__bf16)(acc[e] * inv);
+      *(out_t*)((__bf16*)rec + kE * fj) = ob;
       if (fj == 0) {
-        rec[kD / 2] = M;
-        rec[kD / 2 + 1] = den;
+        rec[D / 2] = M;
+        rec[D / 2 + 1] = den;
       }
     } else if (fin_ok) {
       const float inv = 1.0f / den;
-      bf16x8 ob;
+      out_t ob;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) ob[e] = (__bf16)(acc[e] * inv);
-      *(bf16x8*)(p.out + b * p.q_sb + h * p.q_sh + (int64_t)qfin * p.q_sl + 8 * fj) = ob;
+      for (int e = 0; e < kE; ++e) ob[e] = (__bf16)(acc[e] * inv);
+      *(out_t*)(p.out + b * p.q_sb + h * p.q_sh + (int64_t)qfin * p.q_sl + kE * fj) = ob;
       if (p.lse && fj == 0) p.lse[(int64_t)bh * p.Lq + qfin] = (M + __builtin_amdgcn_logf(den)) * kLn2;
     }
   }
@@ -599,6 +626,17 @@ extern "C" int cover_rect_timing_read(uint64_t* host, int64_t n) {
                                   0, hipMemcpyDeviceToHost);
 }
 #endif
+
+// One round of workgroups of 32 query rows is always shorter than the four-wave kernel's round
+// of 128 (us, d128 Hq32: L100 6.9 against 10.9, L256 7.1 against 12.9; Hq12 L600 9.3 against
+// 18.5; d64 Hq32: L100 5.4 against 8.1, L256 6.1 against 9.9; Hq12 L600 6.8 against 13.5), two
+// rounds are not (Hq32 L512 d128 17.0 against 16.4, d64 12.0 against 11.9; four rounds at L1024
+// d128 40 against 24), because every 32 rows read all the keys again.  (At 64 two workgroups
+// per CU would fit the LDS, but not the registers: spilling, one round takes 7.5-9.)
+bool attn_small(const AttnArgs& a) {
+  return (int64_t)a.B * a.Hq * ((a.L + kTQ - 1) / kTQ) <= 256 &&
+         a.kv_sl < (int64_t(1) << 26);
+}
 
 hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
   RectParams p;
@@ -621,7 +659,9 @@ hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
   if (a.n_split == 1) {
     p.n_wg = (int)n;
     p.xcd_slots = (int)((n + 7) / 8);
-    hipLaunchKernelGGL(cover_attn_tile_kernel<false>, dim3((unsigned)(8 * (int64_t)p.xcd_slots)), block, 0, stream, p);
+    const dim3 grid((unsigned)(8 * (int64_t)p.xcd_slots));
+    if (a.d == 128) hipLaunchKernelGGL((cover_attn_tile_kernel<128, false>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((cover_attn_tile_kernel<64, false>), grid, block, 0, stream, p);
     return hipGetLastError();
   }
   constexpr int64_t kMaxGrid = (int64_t(1) << 23) - 8;  // workgroups per launch: under 2^32 work-items
@@ -629,7 +669,7 @@ hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
     p.first_wg = (int)first;
     p.n_wg = (int)(n - first < kMaxGrid ? n - first : kMaxGrid);
     p.xcd_slots = (p.n_wg + 7) / 8;
-    hipLaunchKernelGGL(cover_attn_tile_kernel<true>, dim3((unsigned)(8 * p.xcd_slots)), block, 0, stream, p);
+    hipLaunchKernelGGL((cover_attn_tile_kernel<128, true>), dim3((unsigned)(8 * p.xcd_slots)), block, 0, stream, p);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

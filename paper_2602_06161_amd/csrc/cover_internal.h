@@ -83,7 +83,7 @@ struct RectArgs {
   void* out;
   float* lse;  // may be null
   float* workspace;
-  int32_t B, Hq, Hkv, L, max_seeds, q_off, Lq, n_split;
+  int32_t B, Hq, Hkv, L, d, max_seeds, q_off, Lq, n_split;
   float scale;  // > 0
   int64_t q_sb, q_sh, q_sl, kv_sb, kv_sh, kv_sl;
 };
@@ -119,7 +119,8 @@ int64_t stats_workspace_floats(int B, int Hq, int Lr);
 // (COVER_STATS_SCRATCH_FLOATS floats), looked up once per device
 hipError_t stats_scratch(float** ptr);
 hipError_t launch_decode_update(const UpdateArgs& a, hipStream_t stream);
-hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream);  // bf16, d = 128
+hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream);  // bf16, d = 128 (n_split 1: or 64)
+bool attn_small(const AttnArgs& a);  // a square call better served by launch_attn_rect (bf16)
 
 // contract checks (COVER_DEBUG=1)
 bool debug_enabled();

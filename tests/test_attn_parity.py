@@ -131,15 +131,21 @@ def test_bf16_every_position_a_seed(d):
     check_attn(out, lse, ref, lref, torch.bfloat16, "all-seeds")
 
 
-@pytest.mark.parametrize("L,n,layout,late", [(32, 17, "head", False), (64, 40, "token", False), (65, 3, "head", False),
-                                             (128, 30, "token", False), (193, 100, "head", False),
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("many", [False, True])
+@pytest.mark.parametrize("L,n,layout,late", [(1, 1, "head", False), (32, 17, "head", False), (64, 40, "token", False),
+                                             (65, 3, "head", False), (193, 100, "head", False),
                                              (449, 25, "token", True), (577, 200, "head", True)])
-def test_bf16_d64_edges(L, n, layout, late):
-    """Head size 64: whole and ragged stages and query tiles, one to ten stages, tiles with more
-    and fewer than 16 seed rows, token-major strides, and (late) scores that outgrow the first
-    stage's by more than 2^24, so the tile is computed again with per-stage rescaling."""
-    announce(f"bf16 d64 L{L} seeds{n} {layout} late {late}")
-    a = _custom(L, 2, 4, 2, L, 64, n)
+def test_bf16_edges_of_both_kernels(d, many, L, n, layout, late):
+    """Up to 256 tiles of 32 query rows a call runs on the block kernel, beyond (many) on the
+    four-wave kernel: whole and ragged stages and query tiles, one to eighteen stages, tiles with
+    more and fewer than 16 seed rows, grouped heads, token-major strides, and (late) scores that
+    outgrow the first stage's by more than 2^24 (rescaled, or the tile computed again)."""
+    per = -(-L // 32)
+    Hq = 2 * (128 // per + 1) if many else 2
+    assert (Hq * per > 256) == many
+    announce(f"bf16 d{d} Hq{Hq} L{L} seeds{n} {layout} late {late}")
+    a = _custom(L, 1, Hq, Hq // 2, L, d, n)
     if late:
         for k in ("k_live", "k_cache"):
             a[k][:, :, 3 * L // 4:] *= 40.0
@@ -148,9 +154,8 @@ def test_bf16_d64_edges(L, n, layout, late):
             a[k] = a[k].transpose(1, 2).contiguous().transpose(1, 2)
     out, lse = _run(a)
     ref, lref = _oracle(a)
-    if late:  # scores of some hundreds: bf16 rounds nothing in them, fp32 sums to 2^-24 of their size
-        assert np.abs(lref).max() > 30
-    check_attn(out, lse, ref, lref, torch.bfloat16, f"L{L}")
+    assert not late or np.abs(lref).max() > 30
+    check_attn(out, lse, ref, lref, torch.bfloat16, f"d{d} L{L} many {many}")
 
 
 def test_zero_seeds_and_no_seed_arrays():
