@@ -1,6 +1,7 @@
 """Build the COVER HIP library for gfx950 (in-tree, hipcc).
 
-Produces ``paper_2602_06161_amd/lib/libcover.so`` from ``csrc/``.  Run as
+Produces ``paper_2602_06161_amd/lib/libcover.so`` and the binding's native part,
+``lib/_cover_host.so``, from ``csrc/``.  Run as
 ``python -m paper_2602_06161_amd.build``; ``__graft_entry__.build()`` calls ``build()``.
 """
 from __future__ import annotations
@@ -19,6 +20,9 @@ OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "lib", "libcover.so")
 # the same library with the attention kernel's phase timestamps compiled in (measurement only)
 LIB_TIMING = os.path.join(PKG, "lib", "libcover_timing.so")
+
+# the Python binding's native part (host code against torch's headers)
+HOST = os.path.join(PKG, "lib", "_cover_host.so")
 
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC") or shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -61,13 +65,38 @@ def _compile(src: str, timing: bool = False) -> str:
     return obj
 
 
+def _build_host() -> None:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
+    tmp = HOST + ".tmp"
+    cmd = [HIPCC, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-I", sysconfig.get_paths()["include"], "-I", os.path.join(rocm, "include")]
+    for path in cpp_extension.include_paths():
+        cmd += ["-I", path]
+    cmd += [os.path.join(CSRC, "host.cpp"), "-o", tmp]
+    for path in cpp_extension.library_paths():
+        cmd += ["-L", path]
+    cmd += ["-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed for host.cpp:\n{' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, HOST)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     os.makedirs(os.path.dirname(LIB), exist_ok=True)
     jobs = ([(src, False) for src in SOURCES] + [(src, True) for src in TIMING]
             + [(src, True) for src in TIMING_ONLY])
-    with ThreadPoolExecutor(max_workers=len(jobs)) as ex:
+    with ThreadPoolExecutor(max_workers=len(jobs) + 1) as ex:
+        host = ex.submit(_build_host)
         built = dict(zip(jobs, ex.map(lambda j: _compile(*j), jobs)))
+        host.result()
     plain = [built[(src, False)] for src in SOURCES]
     timed = [built[(src, src in TIMING)] for src in SOURCES] + [built[(src, True)] for src in TIMING_ONLY]
     for lib, objs in ((LIB, plain), (LIB_TIMING, timed)):
@@ -79,6 +108,8 @@ def build(verbose: bool = True) -> str:
         os.replace(tmp, lib)
         if verbose:
             print(f"built {lib}", file=sys.stderr)
+    if verbose:
+        print(f"built {HOST}", file=sys.stderr)
     return LIB
 
 

@@ -1,8 +1,11 @@
-"""ctypes binding of the COVER C ABI (``include/cover.h``).
+"""Binding of the COVER C ABI (``include/cover.h``): ctypes, and a native form of the calls a
+decoding step makes (``csrc/host.cpp``).
 
 Argument marshalling only: torch supplies device memory and the stream; every step of the
 computation runs in the HIP kernels of ``libcover.so``.  There is no fallback -- if the
-library has not been built, or a call is rejected, an exception is raised.
+libraries have not been built, or a call is rejected, an exception is raised.  A call goes to
+its native form first; that makes it, or hands back what fails a check or is out of the
+ordinary (None) to the Python form below it, which raises the error.
 """
 from __future__ import annotations
 
@@ -12,7 +15,7 @@ import os
 
 import torch
 
-from .build import LIB
+from .build import HOST, LIB
 
 COVER_OK, COVER_ERR_INVALID, COVER_ERR_UNSUPPORTED, COVER_ERR_HIP = 0, -1, -2, -3
 COVER_F32, COVER_BF16 = 0, 1
@@ -81,6 +84,7 @@ def attn_stats_workspace(B: int, Hq: int, Lr: int) -> int:
 
 _lib = None
 _lib_path = LIB
+_host = None
 
 
 def use_library(path: str) -> None:
@@ -90,6 +94,27 @@ def use_library(path: str) -> None:
     if _lib is not None and path != _lib_path:
         raise RuntimeError("the COVER library is already loaded")
     _lib_path = path
+
+
+def host():
+    """The calls' native forms (csrc/host.cpp, built in-tree) on the loaded library."""
+    global _host
+    if _host is None:
+        import importlib.machinery
+        import importlib.util
+
+        if not os.path.exists(HOST):
+            raise RuntimeError(f"the binding's native part is not built ({HOST}); run "
+                               "`python -m paper_2602_06161_amd.build` or __graft_entry__.build()")
+        loader = importlib.machinery.ExtensionFileLoader("_cover_host", HOST)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("_cover_host", loader))
+        loader.exec_module(m)
+        L = lib()
+        m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.cover_attn_fwd, L.cover_select_seeds, L.cover_token_stats, L.cover_token_sample,
+            L.cover_attn_stats, L.cover_attn_stats_workspace, L.cover_decode_update)))
+        _host = m
+    return _host
 
 
 def lib():
@@ -162,6 +187,16 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _raw_stream(stream) -> int:
+    """The HIP stream handle `stream` stands for (None: the current stream; without an initialised
+    GPU 0, which nothing uses: no tensor is on a GPU then)."""
+    if stream is None:
+        if not torch.cuda.is_initialized():
+            return 0
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream if isinstance(stream, int) else stream.cuda_stream
+
+
 def attn_desc(q: torch.Tensor, k: torch.Tensor, max_seeds: int, scale: float = 0.0) -> AttnDesc:
     B, Hq, L, d = q.shape
     Hkv = k.shape[1]
@@ -177,6 +212,12 @@ def cover_attn_fwd(q, k_live, v_live, k_cache, v_cache, seed_idx=None, n_seed=No
     """COVER attention of one layer.  Tensors on the GPU: q [B,Hq,L,d]; k/v [B,Hkv,L,d]
     (head dim contiguous, all four K/V tensors with identical strides); seed_idx int32
     [B,max_seeds]; n_seed int32 [B].  Returns (out, lse)."""
+    done = (_host or host()).attn_fwd(q, k_live, v_live, k_cache, v_cache, seed_idx, n_seed, out, lse,
+                                       scale, want_lse, _raw_stream(stream))
+    if done.__class__ is tuple:
+        return done
+    if done is not None:
+        raise CoverError(done, "cover_attn_fwd")
     for t in (k_live, v_live, k_cache, v_cache):
         if t.shape != k_live.shape or t.stride() != k_live.stride() or t.dtype != q.dtype:
             raise ValueError("k_live, v_live, k_cache, v_cache need equal shape, strides and dtype")
@@ -218,9 +259,17 @@ def rect_splits(B: int, Hq: int, Lq: int, L: int) -> int:
         return 1
     tiles, stages = B * Hq * ((Lq + 31) // 32), -(-L // 32)
     # rounds of 256 workgroups, each as long as its stages and about 18 stages' worth of start
-    # and merge; 24 for the second launch
-    cost = lambda n: -(-tiles * n // 256) * (-(-stages // n) + 18) + (24 if n > 1 else 0)
-    return min(range(1, min(256, -(-L // 128)) + 1), key=cost)
+    # and merge; 24 for the second launch.  The candidates fill 1 to 8 rounds.
+    best, least = 1, stages + 18
+    for rounds in range(1, 9):
+        n = min(256 * rounds // tiles, 256, -(-L // 128))
+        if n > 1:
+            length = -(-stages // n)
+            n = -(-stages // length)  # the fewest splits of that length
+            cost = -(-tiles * n // 256) * (length + 18) + 24
+            if cost < least:
+                best, least = n, cost
+    return best
 
 
 def cover_attn_rect(q, k_live, v_live, k_cache, v_cache, q_off: int, seed_idx=None, n_seed=None,
@@ -273,6 +322,12 @@ def cover_select_seeds(logp, d_in, d_out, flags, max_seeds: int, pos_offset: int
     """Stability-aware seed selection.  logp/d_in/d_out fp32 [B,Lr], flags uint8 [B,Lr] on the
     GPU (contiguous).  Returns (seed_idx int32 [B,max_seeds], n_seed int32 [B], score fp64
     [B,Lr] or None)."""
+    done = (_host or host()).select_seeds(logp, d_in, d_out, flags, max_seeds, pos_offset, seed_idx,
+                                           n_seed, score, want_score, _raw_stream(stream))
+    if done.__class__ is tuple:
+        return done
+    if done is not None:
+        raise CoverError(done, "cover_select_seeds")
     B, Lr = logp.shape
     for t, dt in ((logp, torch.float32), (d_in, torch.float32), (d_out, torch.float32),
                   (flags, torch.uint8)):
@@ -304,6 +359,14 @@ def cover_decode_update(tokens, argmax, conf, seed_idx, n_seed, remask_count, ma
     unless given (None when want_outputs is False).  With last_unmask (int32 [B,Lr], in
     place) the step's flip-flop events go to flipflops (int32 [B], allocated unless given),
     returned as a fourth element."""
+    if last_unmask is None and flipflops is None:
+        done = (_host or host()).decode_update(tokens, argmax, conf, seed_idx, n_seed, remask_count, mask_id,
+                                                tau, draft_cap, remask_budget, pos_offset, flags,
+                                                drafted, counts, want_outputs, min_draft, _raw_stream(stream))
+        if done.__class__ is tuple:
+            return done
+        if done is not None:
+            raise CoverError(done, "cover_decode_update")
     B, Lr = tokens.shape
     for t, dt in ((tokens, torch.int32), (argmax, torch.int32), (conf, torch.float32),
                   (remask_count, torch.int32)):
@@ -348,6 +411,11 @@ def cover_token_sample(logits, temperature: float, seed: int, step: int, want_pr
     """Temperature sampling per row of logits [R, V] (bf16 or fp32, last dimension
     contiguous, row stride a multiple of 16 bytes).  Returns (token int32 [R], prob fp32 [R]
     or None)."""
+    done = (_host or host()).token_sample(logits, temperature, seed, step, want_prob, _raw_stream(stream))
+    if done.__class__ is tuple:
+        return done
+    if done is not None:
+        raise CoverError(done, "cover_token_sample")
     R, V = logits.shape
     dt = {torch.float32: COVER_F32, torch.bfloat16: COVER_BF16}.get(logits.dtype)
     if dt is None or logits.stride(-1) != 1:
@@ -368,6 +436,11 @@ def cover_token_stats(logits, tokens=None, want_logp: bool = True, want_conf: bo
     """Per-row log p(token), max probability and argmax of logits [R, V] (bf16 or fp32, last
     dimension contiguous, row stride a multiple of 16 bytes).  Returns (logp, conf, argmax),
     each None when not requested."""
+    done = (_host or host()).token_stats(logits, tokens, want_logp, want_conf, want_argmax, _raw_stream(stream))
+    if done.__class__ is tuple:
+        return done
+    if done is not None:
+        raise CoverError(done, "cover_token_stats")
     R, V = logits.shape
     dt = {torch.float32: COVER_F32, torch.bfloat16: COVER_BF16}.get(logits.dtype)
     if dt is None or logits.stride(-1) != 1:
@@ -392,6 +465,12 @@ def cover_attn_stats(q, k_live, k_cache, seed_idx, n_seed, lse, masked, drafted,
     """d_in, d_out [B, Lr] over the region [r0, r0+Lr) (Lr = masked.shape[1]) from the corrected
     attention weights of cover_attn_fwd (lse from that call).  bf16 q/k; masked, drafted
     uint8 [B, Lr]."""
+    done = (_host or host()).attn_stats(q, k_live, k_cache, seed_idx, n_seed, lse, masked, drafted, r0,
+                                         scale, workspace, _raw_stream(stream))
+    if done.__class__ is tuple:
+        return done
+    if done is not None:
+        raise CoverError(done, "cover_attn_stats")
     B, Hq, L, d = q.shape
     Lr = masked.shape[1]
     for t in (k_live, k_cache):
