@@ -16,14 +16,15 @@
 // Only masked queries count in d_in and only drafted keys in d_out, so the kernel first lists
 // both (ascending) and multiplies just those rows: d_in takes S = Q_masked K^T over 32-key
 // tiles, d_out takes S^T = K_drafted Q^T over 32-query tiles, the listed rows being the A
-// operand, so that each mass is a sum inside a lane.  One workgroup per (batch row, query head,
-// group of tiles), about 256 in all; both masses of its positions are complete in it and go to a
-// caller-provided workspace, and a second kernel averages them over heads; every sum runs in a
-// fixed order, so the results do not depend on scheduling.  Measured against forming S and S^T
-// over all rows and keys with a mask (B8 H32, 512 positions, 256 masked, 15 drafted): 89 -> 32 us
-// for both launches.  What bounds it now is the vector memory path: a lane reads 16 bytes of its
-// own row, 32 cache lines per load, so a wave that holds two tiles (half the loads per product)
-// takes 32 us and one tile 46; more workgroups per head (a second per CU) do not help (46-48).
+// operand, so that each mass is a sum inside a lane.  The listed rows are gathered into LDS once
+// per workgroup, up to 512 at a time, by global-to-LDS loads; a wave keeps its own tiles' keys
+// and queries in registers.  One workgroup per (batch row, query head, group of tiles), about
+// 256 in all; both masses of its positions are complete in it and go to a caller-provided
+// workspace, and a second kernel averages them over heads; every sum runs in a fixed order, so
+// the results do not depend on scheduling.  Measured (B8 H32, 512 positions, 256 masked, 15
+// drafted): forming S and S^T over all rows and keys with a mask 89 us; listed rows read by every
+// wave on its own 32; through LDS 28.9, of which 14 are the 67 MB of Q and K at the rate HBM is
+// read here and 3.5 the second kernel.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -259,6 +260,8 @@ static_assert(kPos * kStatThreads == COVER_STATS_MAX_LR, "the region is dealt ou
 template <int D, int NK>
 __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const StatParams p) {
   constexpr int KS = D / 16;
+  constexpr int kCap = D == 128 ? 16 : 14;  // units in LDS (D = 64: two workgroups per CU)
+  __shared__ __attribute__((aligned(1024))) char rows[kCap * 32 * 2 * D];
   __shared__ uint64_t seg_m[kSegs], seg_d[kSegs];           // masked / drafted positions
   __shared__ uint32_t sbits[2 * kSegs];                     // seeds
   __shared__ uint16_t list_m[COVER_STATS_MAX_LR], list_d[COVER_STATS_MAX_LR];
@@ -353,14 +356,31 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) f[ks] = *(const bf16x8*)(qbh + (int64_t)j * p.q_sl + (2 * ks + hl) * 8);
   };
+  auto k_row = [&](int j) __attribute__((always_inline)) -> const __bf16* {
+    return (is_seed(j) ? p.kc : p.kl) + kvo + (int64_t)j * p.kv_sl;
+  };
   auto load_k = [&](bf16x8* f, int j) __attribute__((always_inline)) {
-    const __bf16* src = (is_seed(j) ? p.kc : p.kl) + kvo + (int64_t)j * p.kv_sl;
+    const __bf16* src = k_row(j);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) f[ks] = *(const bf16x8*)(src + (2 * ks + hl) * 8);
   };
-  // the rows of a listed tile, one per lane pair (past the list's end: its last entry)
-  auto listed = [&](const uint16_t* list, int n, int t) __attribute__((always_inline)) -> int {
-    return list[min(32 * t + l32, n - 1)];
+  // The units: m_tiles tiles of listed masked queries, then d_tiles tiles of listed drafted keys.
+  // Their rows are gathered into LDS, kCap units at a time, by global-to-LDS loads of kRPL rows
+  // (lane / kCh selects the row, past the list's end its last entry), the 16-byte chunk index
+  // XOR-ed with the row's swizzle, so that the b128 operand reads cover all banks.
+  constexpr int kCh = D / 8, kRPL = 64 / kCh, kLPU = 32 / kRPL;  // loads per unit
+  auto swz = [](int row) __attribute__((always_inline)) -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+  const int units = m_tiles + d_tiles;
+  auto stage = [&](int u0) __attribute__((always_inline)) {
+    const int n = min(units - u0, kCap) * kLPU;
+    for (int i = wave; i < n; i += kStatWaves) {
+      const int u = u0 + i / kLPU, r = (i % kLPU) * kRPL + lane / kCh;
+      const __bf16* src;
+      if (u < m_tiles) src = qbh + (int64_t)list_m[min(32 * u + r, n_m - 1)] * p.q_sl;
+      else src = k_row(list_d[min(32 * (u - m_tiles) + r, n_d - 1)]);
+      __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)(src + ((lane % kCh) ^ swz(r)) * 8),
+                                       (__attribute__((address_space(3))) void*)(rows + i * 1024), 16, 0, 0);
+    }
   };
   // q_j . k_live_j of this lane's position (both halves of d)
   auto live_score = [&](int j) -> float {
@@ -377,14 +397,16 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
   };
 
   // ---- the masses of the workgroup's tiles --------------------------------------------------
-  // wpk waves share a tile's units (its masked-query tiles, then its drafted-key tiles); with
-  // fewer tiles than waves the units are split among them and added in order below.
+  // With up to 4 tiles wpk waves share a tile's units (unit u: wave u % wpk of them) and the sums
+  // are added in order below; otherwise a wave takes NK tiles at a time and all units.
   const int part = p.wpk > 1 ? wave % p.wpk : 0;
-  const int first = kt0 + (p.wpk > 1 ? wave / p.wpk : wave * NK);
-  const int stride = p.wpk > 1 ? kStatWaves / p.wpk : kStatWaves * NK;
-  for (int kt = first; kt < kt1; kt += stride) {
+  const int n_iter = p.wpk > 1 ? 1 : (kt1 - kt0 + kStatWaves * NK - 1) / (kStatWaves * NK);
+  for (int it = 0; it < n_iter; ++it) {
+    const int kt = kt0 + (p.wpk > 1 ? wave / p.wpk : (it * kStatWaves + wave) * NK);
+    const bool active = kt < kt1;
+    if (it == 0 && units > 0) stage(0);
     int jt[NK];            // this lane's position in each tile (clamped into the region)
-    float din[NK], dout[NK];
+    float din[NK], dout[NK], lq[NK];
     uint32_t own[NK];      // positions whose diagonal takes the live key: seed and masked or drafted
     float s_live[NK];
     uint32_t any_own = 0;
@@ -392,25 +414,29 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
     for (int n = 0; n < NK; ++n) {
       const int t = min(kt + n, p.NB - 1);
       jt[n] = min(32 * t + l32, Lr - 1);
-      din[n] = dout[n] = s_live[n] = 0.0f;
+      din[n] = dout[n] = s_live[n] = lq[n] = 0.0f;
       const uint32_t half = 32 * (t & 1);
       own[n] = sbits[t] & ((uint32_t)(seg_m[t >> 1] >> half) | (uint32_t)(seg_d[t >> 1] >> half));
       any_own |= own[n];
+    }
+    // the tiles' rows as B operands: keys for the masked queries, queries for the drafted keys
+    // (requested together, while the units are on their way to LDS)
+    bf16x8 fk[NK][KS], fq[NK][KS];
+    if (active && part < m_tiles) {
+#pragma unroll
+      for (int n = 0; n < NK; ++n) load_k(fk[n], jt[n]);
+    }
+    if (active && ((part - m_tiles) & (p.wpk - 1)) < d_tiles) {
+#pragma unroll
+      for (int n = 0; n < NK; ++n) {
+        load_q(fq[n], jt[n]);
+        lq[n] = lrow[jt[n]];
+      }
     }
     if (__builtin_amdgcn_readfirstlane(any_own) != 0) {
 #pragma unroll
       for (int n = 0; n < NK; ++n) s_live[n] = live_score(jt[n]);
     }
-    // the listed rows (A) against the wave's tiles (B): S in the registers of (row, position)
-    bf16x8 fb[NK][KS], fa[KS], fn[KS];
-    auto product = [&](f32x16* s) __attribute__((always_inline)) {
-#pragma unroll
-      for (int n = 0; n < NK; ++n) s[n] = (f32x16){};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int n = 0; n < NK; ++n) s[n] = mfma16(fa[ks], fb[n][ks], s[n]);
-    };
     // seed rows on their own diagonal: the listed position equals this lane's
     auto diagonal = [&](f32x16* s, const uint16_t* list, int n_list, int t) {
       const int lo = list[32 * t], hi = list[min(32 * t + 31, n_list - 1)];
@@ -424,60 +450,63 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
         }
       }
     };
-    const bool do_in = part < m_tiles;
-    if (do_in) {
-      load_q(fa, listed(list_m, n_m, part));
-#pragma unroll
-      for (int n = 0; n < NK; ++n) load_k(fb[n], jt[n]);
-    }
-    for (int t = part; t < m_tiles; t += p.wpk) {
-      if (t + p.wpk < m_tiles) load_q(fn, listed(list_m, n_m, t + p.wpk));
-      f32x16 s[NK];
-      product(s);
-      if (__builtin_amdgcn_readfirstlane(any_own) != 0) diagonal(s, list_m, n_m, t);
-      f32x4 w4[NK][4];  // a tile's 16 weights are added as a tree, then to the running sum
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 lq = *(const f32x4*)(lse_m + 32 * t + 8 * q + 4 * hl);
-#pragma unroll
-        for (int n = 0; n < NK; ++n)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            w4[n][q][e] = weight(s[n][4 * q + e], lq[e]);
+    for (int u0 = 0; u0 < units; u0 += kCap) {
+      const bool again = u0 > 0 || (it > 0 && units > kCap);
+      if (again) {
+        __syncthreads();  // (every wave is done with the units before)
+        stage(u0);
       }
-#pragma unroll
-      for (int n = 0; n < NK; ++n) din[n] += tree_sum(w4[n]);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) fa[ks] = fn[ks];
-    }
-    // units after the masked tiles: the drafted keys against the tiles' queries
-    const int d_first = ((part - m_tiles) % p.wpk + p.wpk) % p.wpk;
-    if (d_first < d_tiles) {
-      load_k(fa, listed(list_d, n_d, d_first));
-      float lq[NK];
-#pragma unroll
-      for (int n = 0; n < NK; ++n) {
-        load_q(fb[n], jt[n]);
-        lq[n] = lrow[jt[n]];
+      if (again || it == 0) {
+        __builtin_amdgcn_s_waitcnt(0);  // this wave's loads to LDS have landed, so after
+        __syncthreads();                // the barrier have all waves'
       }
-      for (int t = d_first; t < d_tiles; t += p.wpk) {
-        if (t + p.wpk < d_tiles) load_k(fn, listed(list_d, n_d, t + p.wpk));
+      if (!active) continue;
+      const int u1 = min(units, u0 + kCap);
+      for (int u = u0 + ((part - u0) & (p.wpk - 1)); u < u1; u += p.wpk) {
+        // the listed rows (A) against the wave's tiles (B): S in the registers of (row, position)
+        const char* base = rows + (u - u0) * (32 * 2 * D) + l32 * (2 * D);
+        bf16x8 fa[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) fa[ks] = *(const bf16x8*)(base + (((2 * ks + hl) ^ swz(l32)) << 4));
         f32x16 s[NK];
-        product(s);
-        if (__builtin_amdgcn_readfirstlane(any_own) != 0) diagonal(s, list_d, n_d, t);
-        const int lim = n_d - 32 * t - 4 * hl;  // rows past the list's end have no weight
 #pragma unroll
-        for (int n = 0; n < NK; ++n) {
-          f32x4 w4[4];
+        for (int n = 0; n < NK; ++n) s[n] = (f32x16){};
+        if (u < m_tiles) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float w = weight(s[n][r], lq[n]);
-            w4[r >> 2][r & 3] = 8 * (r >> 2) + (r & 3) < lim ? w : 0.0f;
+          for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int n = 0; n < NK; ++n) s[n] = mfma16(fa[ks], fk[n][ks], s[n]);
+          if (__builtin_amdgcn_readfirstlane(any_own) != 0) diagonal(s, list_m, n_m, u);
+          f32x4 w4[NK][4];  // a unit's 16 weights are added as a tree, then to the running sum
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 lm = *(const f32x4*)(lse_m + 32 * u + 8 * q + 4 * hl);
+#pragma unroll
+            for (int n = 0; n < NK; ++n)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) w4[n][q][e] = weight(s[n][4 * q + e], lm[e]);
           }
-          dout[n] += tree_sum(w4);
-        }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = fn[ks];
+          for (int n = 0; n < NK; ++n) din[n] += tree_sum(w4[n]);
+        } else {
+          const int t = u - m_tiles;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int n = 0; n < NK; ++n) s[n] = mfma16(fa[ks], fq[n][ks], s[n]);
+          if (__builtin_amdgcn_readfirstlane(any_own) != 0) diagonal(s, list_d, n_d, t);
+          const int lim = n_d - 32 * t - 4 * hl;  // rows past the list's end have no weight
+#pragma unroll
+          for (int n = 0; n < NK; ++n) {
+            f32x4 w4[4];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float w = weight(s[n][r], lq[n]);
+              w4[r >> 2][r & 3] = 8 * (r >> 2) + (r & 3) < lim ? w : 0.0f;
+            }
+            dout[n] += tree_sum(w4);
+          }
+        }
       }
     }
 #pragma unroll
@@ -485,7 +514,7 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
       din[n] += __shfl_xor(din[n], 32);
       dout[n] += __shfl_xor(dout[n], 32);
       if (p.wpk > 1) {  // (one tile per wave then: TPG <= kStatWaves / wpk)
-        if (hl == 0) {
+        if (hl == 0 && active) {
           part_in[wave][l32] = din[n];
           part_out[wave][l32] = dout[n];
         }

@@ -206,7 +206,8 @@ def test_attn_stats_workload(name):
     (2, 64, 8, 190, 128),                      # three: two waves each
     (1, 256, 8, 33, 128),                      # two tiles, the second of one position
     (2, 128, 8, 250, 64),                      # eight: one wave each
-    (2, 128, 8, 289, 64), (2, 128, 8, 600, 64)])  # ten and nineteen: two tiles per wave
+    (2, 128, 8, 289, 64), (2, 128, 8, 600, 64),  # ten and nineteen: two tiles per wave
+    (1, 4, 2, 1100, 128), (1, 128, 8, 1100, 128)])  # more listed tiles than LDS holds at a time
 def test_attn_stats_lists(B, Hq, Hkv, Lr, d):
     """The lists of masked queries and drafted keys, at every division of a workgroup's waves:
     all or none of the positions masked or drafted, single ones, counts at the edges of a
