@@ -257,11 +257,14 @@ constexpr int kPos = COVER_STATS_MAX_LR / kStatThreads;     // region positions 
 static_assert(kPos * kStatThreads == COVER_STATS_MAX_LR, "the region is dealt out evenly");
 
 // NK: key tiles (and query tiles) a wave holds at a time, so that each gathered row feeds NK MFMAs
-template <int D, int NK>
+// DIRECT: the listed rows are read from memory by the wave that multiplies them (up to two tiles
+// per workgroup, where a row is used once or twice and LDS would only add a round trip: B1 H32,
+// 256 positions 8.9 us a call against 9.9); otherwise through LDS
+template <int D, int NK, bool DIRECT>
 __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const StatParams p) {
   constexpr int KS = D / 16;
   constexpr int kCap = D == 128 ? 16 : 14;  // units in LDS (D = 64: two workgroups per CU)
-  __shared__ __attribute__((aligned(1024))) char rows[kCap * 32 * 2 * D];
+  __shared__ __attribute__((aligned(1024))) char rows[DIRECT ? 1024 : kCap * 32 * 2 * D];
   __shared__ uint64_t seg_m[kSegs], seg_d[kSegs];           // masked / drafted positions
   __shared__ uint32_t sbits[2 * kSegs];                     // seeds
   __shared__ uint16_t list_m[COVER_STATS_MAX_LR], list_d[COVER_STATS_MAX_LR];
@@ -404,7 +407,7 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
   for (int it = 0; it < n_iter; ++it) {
     const int kt = kt0 + (p.wpk > 1 ? wave / p.wpk : (it * kStatWaves + wave) * NK);
     const bool active = kt < kt1;
-    if (it == 0 && units > 0) stage(0);
+    if (!DIRECT && it == 0 && units > 0) stage(0);
     int jt[NK];            // this lane's position in each tile (clamped into the region)
     float din[NK], dout[NK], lq[NK];
     uint32_t own[NK];      // positions whose diagonal takes the live key: seed and masked or drafted
@@ -450,24 +453,28 @@ __global__ __launch_bounds__(kStatThreads) void cover_attn_stats_kernel(const St
         }
       }
     };
-    for (int u0 = 0; u0 < units; u0 += kCap) {
-      const bool again = u0 > 0 || (it > 0 && units > kCap);
+    for (int u0 = 0; u0 < units; u0 += DIRECT ? units : kCap) {
+      const bool again = !DIRECT && (u0 > 0 || (it > 0 && units > kCap));
       if (again) {
         __syncthreads();  // (every wave is done with the units before)
         stage(u0);
       }
-      if (again || it == 0) {
+      if (!DIRECT && (again || it == 0)) {
         __builtin_amdgcn_s_waitcnt(0);  // this wave's loads to LDS have landed, so after
         __syncthreads();                // the barrier have all waves'
       }
       if (!active) continue;
-      const int u1 = min(units, u0 + kCap);
+      const int u1 = DIRECT ? units : min(units, u0 + kCap);
       for (int u = u0 + ((part - u0) & (p.wpk - 1)); u < u1; u += p.wpk) {
         // the listed rows (A) against the wave's tiles (B): S in the registers of (row, position)
         const char* base = rows + (u - u0) * (32 * 2 * D) + l32 * (2 * D);
         bf16x8 fa[KS];
+        if constexpr (DIRECT) {
+          if (u < m_tiles) load_q(fa, list_m[min(32 * u + l32, n_m - 1)]);
+          else load_k(fa, list_d[min(32 * (u - m_tiles) + l32, n_d - 1)]);
+        }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) fa[ks] = *(const bf16x8*)(base + (((2 * ks + hl) ^ swz(l32)) << 4));
+        for (int ks = 0; ks < KS && !DIRECT; ++ks) fa[ks] = *(const bf16x8*)(base + (((2 * ks + hl) ^ swz(l32)) << 4));
         f32x16 s[NK];
 #pragma unroll
         for (int n = 0; n < NK; ++n) s[n] = (f32x16){};
@@ -658,15 +665,18 @@ hipError_t launch_attn_stats(const StatsArgs& a, hipStream_t stream) {
   const int64_t nwg = (int64_t)a.B * a.Hq * p.KG;
   if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
   // Up to 4 tiles per workgroup several waves share one; past 8 a wave holds two at a time, so
-  // that every gathered row feeds two products.
+  // that every listed row feeds two products (32 us against 46 at B8 H32, 512 positions, when
+  // rows came straight from memory).
   p.wpk = p.TPG <= 1 ? 8 : (p.TPG <= 2 ? 4 : (p.TPG <= 4 ? 2 : 1));
   const dim3 grid((unsigned)nwg), block(kStatThreads);
   if (a.d == 128) {
-    if (p.TPG > 8) hipLaunchKernelGGL((cover_attn_stats_kernel<128, 2>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((cover_attn_stats_kernel<128, 1>), grid, block, 0, stream, p);
+    if (p.TPG <= 2) hipLaunchKernelGGL((cover_attn_stats_kernel<128, 1, true>), grid, block, 0, stream, p);
+    else if (p.TPG <= 8) hipLaunchKernelGGL((cover_attn_stats_kernel<128, 1, false>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((cover_attn_stats_kernel<128, 2, false>), grid, block, 0, stream, p);
   } else {
-    if (p.TPG > 8) hipLaunchKernelGGL((cover_attn_stats_kernel<64, 2>), grid, block, 0, stream, p);
-    else hipLaunchKernelGGL((cover_attn_stats_kernel<64, 1>), grid, block, 0, stream, p);
+    if (p.TPG <= 2) hipLaunchKernelGGL((cover_attn_stats_kernel<64, 1, true>), grid, block, 0, stream, p);
+    else if (p.TPG <= 8) hipLaunchKernelGGL((cover_attn_stats_kernel<64, 1, false>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((cover_attn_stats_kernel<64, 2, false>), grid, block, 0, stream, p);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
