@@ -4,9 +4,11 @@
 // token currently placed there (u = -log p, Sec. 5.3), the maximum probability (the
 // confidence of Sec. 3) and the token attaining it.  One workgroup of 1024 threads per row;
 // each thread streams 16-byte chunks with four loads in flight and keeps an online (max, sum
-// of exp) pair and the chunk where its max was last raised (the index inside it is found at
-// the end), merged across the workgroup.  The placed token and its logit are fetched at the
-// start by scalar loads, so no memory round trip is left for the end.
+// of exp) pair and the chunk where its max was last raised, merged across the workgroup; the
+// index inside that chunk is found at the end, by the threads that hold the row's maximum.  The
+// placed token and its logit are fetched at the start by scalar loads.  HBM bounds it: 256 rows of
+// 126464 bf16 logits (65 MB) 13.2 us, 15.0 when every thread read its best chunk again (a line
+// from memory each, a quarter of the logits' bytes); 512 rows, cold, 29.1 -> 25.4.
 //
 // cover_attn_stats_kernel + cover_attn_stats_reduce_kernel: the in/out attention masses of
 // Sec. 5.3 over a response region [r0, r0+Lr), from the last layer's corrected weights
@@ -55,23 +57,6 @@ struct TokParams {
   int V;
 };
 
-// (m, s, i): running max, sum of exp2((x - m) * log2e) over the elements seen, the smallest
-// index holding m.  Merging two triples keeps the larger max (smaller index on ties).
-struct Acc {
-  float m, s;
-  int i;
-};
-__device__ __forceinline__ Acc merge(Acc a, Acc b) {
-  const float m = fmaxf(a.m, b.m);
-  Acc r;
-  r.m = m;
-  const float sa = a.s == 0.0f ? 0.0f : a.s * __builtin_amdgcn_exp2f((a.m - m) * kLog2e);
-  const float sb = b.s == 0.0f ? 0.0f : b.s * __builtin_amdgcn_exp2f((b.m - m) * kLog2e);
-  r.s = sa + sb;
-  r.i = a.m > b.m ? a.i : (b.m > a.m ? b.i : min(a.i, b.i));
-  return r;
-}
-
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
@@ -93,9 +78,10 @@ __device__ __forceinline__ void unpack(u32x4 v, float* x) {
 // a max over the chunk, then one exp2 per element into the sum.
 template <bool BF>
 __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const TokParams p) {
+#pragma clang fp contract(off)  // (the references below are rounded once, where they are formed)
   constexpr int N = BF ? 8 : 4;  // elements per 16-byte chunk
   __shared__ float sm[kTokThreads / 64], ss[kTokThreads / 64];
-  __shared__ int si[kTokThreads / 64];
+  __shared__ int si;
   const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const char* row = p.logits + (int64_t)r * p.row_stride_bytes;
   auto chunk = [&](int c) __attribute__((always_inline)) {
@@ -115,17 +101,21 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
       }
     }
   }
-  float m = -INFINITY, s = 0.0f;
+  // s sums exp2(x log2 e + nm) with nm = -m log2 e rounded once: every term, rescaling and merge
+  // uses that same rounded reference, and its rounding is taken out of the row's sum at the end
+  float m = -INFINITY, nm = INFINITY, s = 0.0f;
   int cbest = -1;
   auto fold = [&](const float* x, int c) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
     float cm = x[0];
 #pragma unroll
     for (int e = 1; e < N; ++e) cm = __builtin_fmaxf(cm, x[e]);
     const float mn = __builtin_fmaxf(m, cm);
-    s *= __builtin_amdgcn_exp2f((m - mn) * kLog2e);  // 1 unless the max was raised
+    const float nn = -mn * kLog2e;
+    s *= __builtin_amdgcn_exp2f(nn - nm);  // 1 unless the max was raised
     cbest = cm > m ? c : cbest;
     m = mn;
-    const float nm = -mn * kLog2e;
+    nm = nn;
     float a[N / 2];
 #pragma unroll
     for (int e = 0; e < N / 2; ++e)
@@ -167,51 +157,68 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
       }
     }
   }
-  // index of the maximum: the first element of the best chunk that holds it
-  int ibest = 0x7fffffff;
-  if (cbest >= 0) {
-    float x[N];
-    unpack<BF>(chunk(cbest), x);
-#pragma unroll
-    for (int e = N - 1; e >= 0; --e)
-      if (x[e] == m) ibest = cbest * N + e;
-  }
-  Acc acc = {m, s, ibest};
   // the tail: one element per thread, read at its own width (never past the row's end)
+  int ibest = 0x7fffffff;  // index of the thread's maximum, unless it is in chunk cbest
   if (tid < p.V - nfull * N) {
     const int j = nfull * N + tid;
     const float xj = BF ? __uint_as_float((uint32_t)(*(const uint16_t*)(row + (int64_t)j * 2)) << 16)
                         : *(const float*)(row + (int64_t)j * 4);
-    acc = merge(acc, Acc{xj, 1.0f, j});
+    if (xj > m) {
+      const float nn = -xj * kLog2e;
+      s = (s == 0.0f ? 0.0f : s * __builtin_amdgcn_exp2f(nn - nm)) + __builtin_amdgcn_exp2f(__builtin_fmaf(xj, kLog2e, nn));
+      m = xj;
+      nm = nn;
+      ibest = j;
+      cbest = -1;
+    } else {
+      s += __builtin_amdgcn_exp2f(__builtin_fmaf(xj, kLog2e, nm));
+    }
   }
-  // wave, then workgroup
+  // The row's maximum first: then only the threads that hold it read their best chunk again (a
+  // line from HBM each: when every thread did, that was a quarter of the logits' bytes), while
+  // the sums, on the common maximum, are added.
+  float wm = m;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    Acc o;
-    o.m = __shfl_xor(acc.m, off);
-    o.s = __shfl_xor(acc.s, off);
-    o.i = __shfl_xor(acc.i, off);
-    acc = merge(acc, o);
-  }
-  if (lane == 0) { sm[wave] = acc.m; ss[wave] = acc.s; si[wave] = acc.i; }
+  for (int off = 32; off >= 1; off >>= 1) wm = __builtin_fmaxf(wm, __shfl_xor(wm, off));
+  if (lane == 0) sm[wave] = wm;
+  if (tid == 0) si = 0x7fffffff;
   __syncthreads();
-  if (wave == 0) {  // the 16 wave results: a tree over lanes 0..15 of wave 0
-    constexpr int W = kTokThreads / 64;
-    Acc t = lane < W ? Acc{sm[lane], ss[lane], si[lane]} : Acc{-INFINITY, 0.0f, 0x7fffffff};
+  float M = sm[0];
 #pragma unroll
-    for (int off = W / 2; off >= 1; off >>= 1) {
-      Acc o;
-      o.m = __shfl_xor(t.m, off);
-      o.s = __shfl_xor(t.s, off);
-      o.i = __shfl_xor(t.i, off);
-      t = merge(t, o);
+  for (int w = 1; w < kTokThreads / 64; ++w) M = __builtin_fmaxf(M, sm[w]);
+  const bool holds = m == M;
+  u32x4 best = {};
+  if (holds && cbest >= 0) best = chunk(cbest);
+  const float nM = -M * kLog2e;
+  float t = s == 0.0f ? 0.0f : s * __builtin_amdgcn_exp2f(nM - nm);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+  if (lane == 0) ss[wave] = t;
+  if (holds) {  // the first element of the best chunk that holds the maximum; ties: the smallest
+    if (cbest >= 0) {
+      float x[N];
+      unpack<BF>(best, x);
+#pragma unroll
+      for (int e = N - 1; e >= 0; --e)
+        if (x[e] == M) ibest = cbest * N + e;
     }
-    if (lane == 0) {
-      const float lz = t.m + __builtin_amdgcn_logf(t.s) * kLn2;  // natural log-sum-exp
-      if (p.conf) p.conf[r] = 1.0f / t.s;                         // exp(max - lz)
-      if (p.argmax) p.argmax[r] = t.i;
-      if (p.logp) p.logp[r] = xy - lz;
-    }
+    atomicMin(&si, ibest);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float a[kTokThreads / 64];
+#pragma unroll
+    for (int w = 0; w < kTokThreads / 64; ++w) a[w] = ss[w];
+#pragma unroll
+    for (int n = kTokThreads / 128; n >= 1; n >>= 1)
+#pragma unroll
+      for (int w = 0; w < n; ++w) a[w] += a[w + n];
+    // the sum is 2^c times that of exp(x - M), c the rounding of nM
+    const float c = __builtin_fmaf(M, kLog2e, nM);
+    const float lz = __builtin_fmaf(__builtin_amdgcn_logf(a[0]) - c, kLn2, M);  // natural log-sum-exp
+    if (p.conf) p.conf[r] = __builtin_fmaf(c, kLn2, 1.0f) / a[0];    // exp(max - lz)
+    if (p.argmax) p.argmax[r] = si;
+    if (p.logp) p.logp[r] = xy - lz;
   }
 }
 

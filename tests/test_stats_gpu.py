@@ -79,6 +79,33 @@ def test_token_stats_ties_and_bad_tokens():
     assert np.array_equal(am[ok], r_am)
 
 
+@pytest.mark.parametrize("dtype,V", [("bf16", 5), ("f32", 3), ("bf16", 8197), ("f32", 4099), ("bf16", 65539), ("f32", 32771)])
+def test_token_stats_where_the_maximum_lies(dtype, V):
+    """The row's maximum in the first and last whole chunk, in the tail past the last one, tied
+    within a chunk, across waves and with the tail (the smallest index wins), and large logits
+    (the sum's reference is a rounded product of the maximum)."""
+    announce(f"token stats maximum positions {dtype} V {V}")
+    t = synth.token_inputs(8, V, seed=V, dtype=dtype)
+    x = t["buffer"]
+    top = x[:, :V].max().item() + 1.0
+    n = 8 if dtype == "bf16" else 4
+    last = max(V // n * n - 1, 0)
+    marks = [(0,), (last,), (V - 1,), (min(1, last), min(2, last)), (V // 2, V - 1), (0, V // 2, last), (V - 2,), (0, V - 1)]
+    for r, where in enumerate(marks):
+        for j in where:
+            x[r, j] = top
+    x[6, :V] = x[6, :V] * 8.0 + 300.0
+    lg, cf, am = cover.cover_token_stats(x.cuda()[:, :V], t["tokens"].cuda())
+    torch.cuda.synchronize()
+    xd = x[:, :V].double()
+    lz = torch.logsumexp(xd, 1)
+    want = xd.gather(1, t["tokens"].long()[:, None])[:, 0] - lz
+    assert all(am[r].item() == int((xd[r] == xd[r].max()).nonzero()[0]) for r in range(8))
+    # logp: fp32 rounding of numbers up to |x| (2^-24 of 600, twice) and of the sum
+    np.testing.assert_allclose(lg.cpu().numpy(), want.numpy(), atol=1e-4, rtol=0)
+    np.testing.assert_allclose(cf.cpu().numpy(), torch.exp(xd.max(1).values - lz).numpy(), rtol=TOK_RTOL)
+
+
 def _stats_case(a, r0, masked, drafted):
     t = {k: a[k].cuda() for k in ("q", "k_live", "v_live", "k_cache", "v_cache", "seed_idx", "n_seed")}
     _, lse = cover.cover_attn_fwd(t["q"], t["k_live"], t["v_live"], t["k_cache"], t["v_cache"],
