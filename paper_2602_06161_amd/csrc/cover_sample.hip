@@ -160,12 +160,17 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
   };
   // The bounds that follow from `best`, slackened by the rounding of the scores (2^-24 of their
   // size in each operation): xmin, and the offset of the test in `race`.
-  const float c23 = c * 8388608.0f;
+  // Where the products leave fp32's range (c or the scores beyond kWild) nothing is skipped by
+  // the second, and the first counts from the largest finite score.
+  constexpr float kWild = 1.0e30f, kMaxFloat = 3.402823466e38f;
+  const bool wild = !(c < kWild);
+  const float c23 = wild ? 0.0f : c * 8388608.0f;
   float k23 = INFINITY;
   auto set_bound = [&]() __attribute__((always_inline)) {
+    best = fminf(best, kMaxFloat);
     const float slack = 0.0625f + 1.0e-5f * __builtin_fabsf(best);
     xmin = (best - kMaxAdvantage - slack) * rc;
-    k23 = (127.0f - best + slack) * 8388608.0f;
+    k23 = wild || !(__builtin_fabsf(best) < kWild) ? INFINITY : (127.0f - best + slack) * 8388608.0f;
   };
   // The race of this lane's quad (lanes with `on`).  A token takes part only if its score
   // reaches the row's best, E <= 2^t with t = z / ln 2 - best.  Without a logarithm or an
@@ -366,7 +371,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
       a.m = a.bx;
     }
     if (lane == 0) {
-      p.token[r] = a.i;
+      p.token[r] = a.i < p.V ? a.i : 0;  // (no token, no race: only NaN in the row)
       if (p.prob) p.prob[r] = __builtin_amdgcn_exp2f((a.bx - a.m) * c) / a.s;
     }
   }
@@ -381,7 +386,8 @@ hipError_t launch_token_sample(const SampleArgs& a, hipStream_t stream) {
   p.prob = a.prob;
   p.row_stride_bytes = a.row_stride * (a.bf16 ? 2 : 4);
   p.V = a.V;
-  p.inv_t = 1.0f / a.temperature;
+  const float inv_t = 1.0f / a.temperature;
+  p.inv_t = inv_t < 0x1p127f ? inv_t : 0x1p127f;  // (infinite below T = 2^-128: then 0 / T was NaN)
   p.k0 = (uint32_t)(a.seed & 0xffffffffu);
   p.k1 = (uint32_t)(a.seed >> 32);
   p.step = a.step;

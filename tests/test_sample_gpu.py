@@ -86,3 +86,38 @@ def test_sample_skips_only_losers(R, V, dtype, T):
         assert y[r].max() - y[r, tok[r]] <= 1e-4 * max(1.0, abs(y[r].max())), f"row {r}: not a near tie"
     assert (~same).sum() <= max(1, R // 50)
     assert np.allclose(prob[same], rp[same], rtol=1e-4, atol=1e-7)
+
+
+@pytest.mark.parametrize("R,V,dtype", [(9, 4099, "f32"), (9, 8200, "bf16"), (270, 1003, "f32"), (9, 6, "bf16")])
+def test_sample_stays_in_range(R, V, dtype):
+    """Rows outside the contract, and finite logits whose quotient by T is not: +inf in the first
+    round of loads, in a later one and in several places, -inf everywhere, NaN among ordinary
+    logits and alone, quotients beyond fp32 at both ends.  The token indexes an embedding, so it
+    is in [0, V) whatever the row; where the row has +inf or ordinary logits beside -inf and NaN
+    it is one that holds no less."""
+    announce(f"token sample range R{R} V{V} {dtype}")
+    rng = np.random.default_rng(V)
+    x = rng.normal(0, 2, (R, V))
+    kinds = [lambda r: r.__setitem__(0, np.inf), lambda r: r.__setitem__(V - 1, np.inf),
+             lambda r: r.__setitem__(slice(V // 3, V // 3 + 2), np.inf), lambda r: r.fill(-np.inf),
+             lambda r: r.__setitem__(slice(0, V // 2), np.nan), lambda r: r.fill(np.nan),
+             lambda r: r.__setitem__(V // 2, 3.0e38), lambda r: r.fill(-3.0e38), lambda r: None]
+    for r in range(R):
+        kinds[r % len(kinds)](x[r])
+    dt = synth.TORCH_DTYPE[dtype]
+    per = 8 if dtype == "bf16" else 4
+    buf = torch.zeros((R, (V + per - 1) // per * per), dtype=dt)
+    buf[:, :V] = torch.from_numpy(x).to(dt)
+    for T in (0.1, 1.0e-6, 1.0e-40, 1.0e30):
+        tok, _ = cover.cover_token_sample(buf.cuda()[:, :V], T, 3, 1)
+        torch.cuda.synchronize()
+        tok = tok.cpu().numpy()
+        assert ((0 <= tok) & (tok < V)).all(), f"T {T}: {tok.min()} .. {tok.max()}"
+        for r in range(R):
+            got = x[r, tok[r]]
+            if np.isposinf(x[r]).any():
+                assert np.isposinf(got), f"T {T} row {r}"
+            elif not np.isnan(x[r]).all():
+                assert not np.isnan(got), f"T {T} row {r}"
+            if r % len(kinds) == 6 and T <= 0.1:
+                assert tok[r] == V // 2, f"T {T} row {r}"
