@@ -42,6 +42,7 @@ struct SampleParams {
   int64_t row_stride_bytes;
   int V;
   float inv_t;  // 1 / T
+  double c64;   // log2 e / T
   uint32_t k0, k1, step;
 };
 
@@ -72,23 +73,32 @@ __device__ __forceinline__ u32x4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
 }
 
 // The Gumbel-max draw argmax_v (z_v - ln(-ln u_v)), z = x / T, as an exponential race: with
-// E_v = -log2 u_v (1 / ln 2 times an Exp(1) variable) token v beats b when
-// exp(z_v - z_b) E_b > E_v.
+// E_v = -log2 u_v (1 / ln 2 times an Exp(1) variable) the token with the largest score
+// z_v / ln 2 - log2 E_v wins, the smaller index on equal scores.  The score is a number of the
+// token alone, so who wins does not depend on who meets whom in which order, and it is formed in
+// 64 bits (the logarithm from E's exponent and, in fp32, its mantissa), which the few tokens that
+// come this far afford: to 2^-22 whatever the size of z.
 __device__ __forceinline__ float race_e(uint32_t w) {  // -log2 u > 0
   const float u = __builtin_fmaf((float)(w >> 9), 1.1920928955078125e-7f, 5.9604644775390625e-8f);  // ((w >> 9) + 1/2) 2^-23
   return -__builtin_amdgcn_logf(u);
+}
+__device__ __forceinline__ double score(float x, float E, double c64) {
+  const double l = (double)__builtin_amdgcn_frexp_expf(E) + (double)__builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(E));
+  return __builtin_fma((double)x, c64, -l);
 }
 // scores are z / ln 2 - log2 E: the largest and smallest -log2 E (u = 1 - 2^-24 and 2^-24)
 constexpr float kMaxAdvantage = 23.48f;
 constexpr float kMinAdvantage = -4.585f;
 
 struct Acc {
-  float bx;  // the best token so far: its logit (-inf: none yet)
-  float bE;  // its E
-  int i;     // its index
-  float m;   // reference of the sum (the largest logit, at least kFloor)
-  float s;   // sum of exp((x - m) / T)
+  double sc;  // the best token so far: its score
+  float bx;   // its logit
+  int i;      // its index
+  float m;    // reference of the sum (the largest logit, at least kFloor)
+  float s;    // sum of exp((x - m) / T)
 };
+__device__ __forceinline__ bool beats(double sc, int i, const Acc& a) { return sc > a.sc || (sc == a.sc && i < a.i); }
+
 // the reference of the sum never goes below this, so that a first chunk of masked logits (-inf,
 // or the type's lowest value) adds zeros and not NaN
 constexpr float kFloor = -1.0e30f;
@@ -97,10 +107,9 @@ __device__ __forceinline__ Acc merge(Acc a, Acc b, float c) {
   const float m = fmaxf(a.m, b.m);
   a.s = a.s * __builtin_amdgcn_exp2f((a.m - m) * c) + b.s * __builtin_amdgcn_exp2f((b.m - m) * c);
   a.m = m;
-  const float l = __builtin_amdgcn_exp2f((b.bx - a.bx) * c) * a.bE;  // NaN when neither has a token
-  if (l > b.bE || (l == b.bE && b.i < a.i)) {
+  if (beats(b.sc, b.i, a)) {
+    a.sc = b.sc;
     a.bx = b.bx;
-    a.bE = b.bE;
     a.i = b.i;
   }
   return a;
@@ -137,7 +146,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
   if (tid == 0) s_best = order_int(-INFINITY);
   __syncthreads();
 
-  Acc acc = {-INFINITY, 1.0f, 0x7fffffff, kFloor, 0.0f};
+  Acc acc = {-INFINITY, -INFINITY, 0x7fffffff, kFloor, 0.0f};
   float best = -INFINITY, xmin = -INFINITY;  // the row's best score known here; logits below xmin cannot win
   auto values = [&](const uint32_t* w, float* x) __attribute__((always_inline)) {
     if constexpr (BF) {
@@ -147,15 +156,12 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
       for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(w[e]);
     }
   };
-  // Quads reach a lane in any order: a tie goes to the smaller index explicitly.
   auto race1 = [&](float x, float E, int v) __attribute__((always_inline)) {
-    const float l = __builtin_amdgcn_exp2f((x - acc.bx) * c) * acc.bE;
-    if (l >= E) {
-      if (l > E || v < acc.i) {
-        acc.bx = x;
-        acc.bE = E;
-        acc.i = v;
-      }
+    const double sc = score(x, E, p.c64);
+    if (beats(sc, v, acc)) {
+      acc.sc = sc;
+      acc.bx = x;
+      acc.i = v;
     }
   };
   // The bounds that follow from `best`, slackened by the rounding of the scores (2^-24 of their
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
 #pragma unroll
       for (int e = 0; e < 4; ++e) race1(x[e], race_e(rnd[e]), 4 * (int)q + e);
     }
-    float sc = acc.bx * c - __builtin_amdgcn_logf(acc.bE);
+    float sc = (float)acc.sc;
     if (__builtin_amdgcn_ballot_w64(sc > best) == 0) return;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sc = fmaxf(sc, __shfl_xor(sc, o));
@@ -347,7 +353,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
     for (int o = 32; o > 0; o >>= 1) {
       Acc b;
       b.bx = __shfl_xor(a.bx, o);
-      b.bE = __shfl_xor(a.bE, o);
+      b.sc = __shfl_xor(a.sc, o);
       b.i = __shfl_xor(a.i, o);
       b.m = __shfl_xor(a.m, o);
       b.s = __shfl_xor(a.s, o);
@@ -359,7 +365,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
   if (lane == 0) red[wave] = acc;
   __syncthreads();
   if (wave == 0) {
-    Acc a = lane < kThreads / 64 ? red[lane] : Acc{-INFINITY, 1.0f, 0x7fffffff, kFloor, 0.0f};
+    Acc a = lane < kThreads / 64 ? red[lane] : Acc{-INFINITY, -INFINITY, 0x7fffffff, kFloor, 0.0f};
     a = wave_merge(a);
     if (a.s == 0.0f && p.prob) {
       // every logit of the row is below kFloor: the sum again, relative to the token drawn
@@ -387,6 +393,7 @@ hipError_t launch_token_sample(const SampleArgs& a, hipStream_t stream) {
   p.row_stride_bytes = a.row_stride * (a.bf16 ? 2 : 4);
   p.V = a.V;
   const float inv_t = 1.0f / a.temperature;
+  p.c64 = 1.4426950408889634 / (double)a.temperature;
   p.inv_t = inv_t < 0x1p127f ? inv_t : 0x1p127f;  // (infinite below T = 2^-128: then 0 / T was NaN)
   p.k0 = (uint32_t)(a.seed & 0xffffffffu);
   p.k1 = (uint32_t)(a.seed >> 32);

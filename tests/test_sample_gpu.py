@@ -121,3 +121,31 @@ def test_sample_stays_in_range(R, V, dtype):
                 assert not np.isnan(got), f"T {T} row {r}"
             if r % len(kinds) == 6 and T <= 0.1:
                 assert tok[r] == V // 2, f"T {T} row {r}"
+
+
+def test_sample_repeats_at_near_ties():
+    """64 tokens per row whose perturbed scores agree within fp32 rounding of their logits, and
+    whole rows of one level (in two of these calls two tokens share the largest u exactly): the
+    draw is the same in every launch and for both workgroup sizes, and a token of the largest
+    score.  1e-6: the score's error, 2^-23 of E in its logarithm and 2^-24 in the mantissa's."""
+    announce("token sample near ties")
+    R, V, T = 300, 4096, 0.5
+    rng = np.random.default_rng(8)
+    for step in (1, 11):
+        u = oracle.sample_uniforms(R, V, 77, step)
+        g = -np.log(-np.log(u))
+        near = np.full((R, V), -40.0, np.float32)
+        for r in range(R):
+            at = rng.choice(V, 64, replace=False)
+            near[r, at] = (np.float64(np.float32(T)) * (7.0 - g[r, at])).astype(np.float32)
+        for name, x in (("near", near), ("flat", np.full((R, V), 1.5, np.float32))):
+            dev = torch.from_numpy(x).cuda()
+            draws = [cover.cover_token_sample(dev, T, 77, step)[0].cpu().numpy() for _ in range(8)]
+            draws += [cover.cover_token_sample(dev[:200], T, 77, step)[0].cpu().numpy() for _ in range(8)]
+            for d in draws[1:]:
+                assert np.array_equal(d, draws[0][: len(d)]), f"{name} step {step}: {(d != draws[0][:len(d)]).sum()} rows differ"
+            y = x.astype(np.float64) / T + g
+            if name == "flat":
+                assert (np.sort(u, 1)[:, -1] == np.sort(u, 1)[:, -2]).any()
+                assert np.array_equal(draws[0], y.argmax(1))
+            assert (y.max(1) - y[np.arange(R), draws[0]]).max() <= 1e-6
