@@ -33,16 +33,14 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const u32x4 gu32x4;
 
-constexpr float kLog2e = 1.44269504088896341f;
-
 struct SampleParams {
   const char* logits;
   int32_t* token;
   float* prob;
   int64_t row_stride_bytes;
   int V;
-  float inv_t;  // 1 / T
-  double c64;   // log2 e / T
+  float c;  // log2 e / T
+  double c64;
   uint32_t k0, k1, step;
 };
 
@@ -94,8 +92,8 @@ struct Acc {
   double sc;  // the best token so far: its score
   float bx;   // its logit
   int i;      // its index
-  float m;    // reference of the sum (the largest logit, at least kFloor)
-  float s;    // sum of exp((x - m) / T)
+  float nm;   // reference of the sum: -m c rounded once, m the largest logit (at least kFloor)
+  float s;    // sum of exp2(x c + nm)
 };
 __device__ __forceinline__ bool beats(double sc, int i, const Acc& a) { return sc > a.sc || (sc == a.sc && i < a.i); }
 
@@ -103,10 +101,18 @@ __device__ __forceinline__ bool beats(double sc, int i, const Acc& a) { return s
 // or the type's lowest value) adds zeros and not NaN
 constexpr float kFloor = -1.0e30f;
 
-__device__ __forceinline__ Acc merge(Acc a, Acc b, float c) {
-  const float m = fmaxf(a.m, b.m);
-  a.s = a.s * __builtin_amdgcn_exp2f((a.m - m) * c) + b.s * __builtin_amdgcn_exp2f((b.m - m) * c);
-  a.m = m;
+// The factor that takes a sum from reference nm to nn <= nm: the difference of the two rounded
+// references, so that every term of the row's sum has the same one and its rounding cancels in the
+// quotient at the end (a row's largest term is then exactly the numerator of its token: no
+// probability above 1).  Both infinite, from products beyond fp32: the sum is 0 and stays it.
+__device__ __forceinline__ float rescale(float nm, float nn) {
+#pragma clang fp contract(off)
+  return __builtin_amdgcn_exp2f(fminf(nn - nm, 0.0f));
+}
+__device__ __forceinline__ Acc merge(Acc a, Acc b) {
+  const float nm = fminf(a.nm, b.nm);
+  a.s = a.s * rescale(a.nm, nm) + b.s * rescale(b.nm, nm);
+  a.nm = nm;
   if (beats(b.sc, b.i, a)) {
     a.sc = b.sc;
     a.bx = b.bx;
@@ -130,6 +136,7 @@ constexpr int kQueue = 63 + kDense - 1;  // a wave's queue: up to 63 left over, 
 // kThreads threads per row, kUnroll 16-byte loads per thread in flight
 template <bool BF, int kThreads, int kUnroll>
 __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const SampleParams p) {
+#pragma clang fp contract(off)  // (the sum's references are rounded once, where they are formed)
   constexpr int N = BF ? 8 : 4;   // elements per 16-byte chunk
   constexpr int QPC = N / 4;      // quads per chunk
   constexpr int W = BF ? 2 : 4;   // 32-bit words per quad
@@ -141,12 +148,13 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const char* row = p.logits + (int64_t)r * p.row_stride_bytes;
   const int nfull = p.V / N;
-  const float c = p.inv_t * kLog2e;  // x -> log2 units
+  const float c = p.c;  // x -> log2 units
   const float rc = 1.0f / c;
   if (tid == 0) s_best = order_int(-INFINITY);
   __syncthreads();
 
-  Acc acc = {-INFINITY, -INFINITY, 0x7fffffff, kFloor, 0.0f};
+  float m = kFloor;  // the largest logit of this thread (at least kFloor)
+  Acc acc = {-INFINITY, -INFINITY, 0x7fffffff, -(kFloor * c), 0.0f};
   float best = -INFINITY, xmin = -INFINITY;  // the row's best score known here; logits below xmin cannot win
   auto values = [&](const uint32_t* w, float* x) __attribute__((always_inline)) {
     if constexpr (BF) {
@@ -248,6 +256,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
   };
   // the sum of exponentials over one chunk; returns the largest logit of each quad
   auto fold = [&](const u32x4& raw, float* mx) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
     float x[N];
     float cm = kFloor;
 #pragma unroll
@@ -257,8 +266,8 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
       mx[k] = fmaxf(fmaxf(fmaxf(x[4 * k], x[4 * k + 1]), x[4 * k + 2]), x[4 * k + 3]);
       cm = fmaxf(cm, mx[k]);
     }
-    const float mn = fmaxf(acc.m, cm);
-    const float nm = -mn * c;
+    m = fmaxf(m, cm);
+    const float nm = -(m * c);
     float t[N / 2];
 #pragma unroll
     for (int e = 0; e < N / 2; ++e)
@@ -267,8 +276,8 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
     float sum = t[0];
 #pragma unroll
     for (int e = 1; e < N / 2; ++e) sum += t[e];
-    acc.s = acc.s * __builtin_amdgcn_exp2f((acc.m - mn) * c) + sum;
-    acc.m = mn;
+    acc.s = acc.s * rescale(acc.nm, nm) + sum;
+    acc.nm = nm;
   };
   // (unconditional loads, so that a round's loads stay in flight across the work on the round
   // before; a chunk past the end repeats the last one and is blanked to -inf below)
@@ -342,9 +351,9 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
     const int v = nfull * N + tid;
     const float x = element(v);
     const u32x4 w = philox((uint32_t)(v >> 2), r, p.step, 0u, p.k0, p.k1);
-    const float mn = fmaxf(acc.m, x);
-    acc.s = acc.s * __builtin_amdgcn_exp2f((acc.m - mn) * c) + __builtin_amdgcn_exp2f((x - mn) * c);
-    acc.m = mn;
+    const float nm = -(fmaxf(m, x) * c);
+    acc.s = acc.s * rescale(acc.nm, nm) + __builtin_amdgcn_exp2f(__builtin_fmaf(x, c, nm));
+    acc.nm = nm;
     race1(x, race_e(w[v & 3]), v);
   }
   // merge: across the wave, then the waves
@@ -355,9 +364,9 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
       b.bx = __shfl_xor(a.bx, o);
       b.sc = __shfl_xor(a.sc, o);
       b.i = __shfl_xor(a.i, o);
-      b.m = __shfl_xor(a.m, o);
+      b.nm = __shfl_xor(a.nm, o);
       b.s = __shfl_xor(a.s, o);
-      a = merge(a, b, c);
+      a = merge(a, b);
     }
     return a;
   };
@@ -365,8 +374,9 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
   if (lane == 0) red[wave] = acc;
   __syncthreads();
   if (wave == 0) {
-    Acc a = lane < kThreads / 64 ? red[lane] : Acc{-INFINITY, -INFINITY, 0x7fffffff, kFloor, 0.0f};
+    Acc a = lane < kThreads / 64 ? red[lane] : Acc{-INFINITY, -INFINITY, 0x7fffffff, -(kFloor * c), 0.0f};
     a = wave_merge(a);
+    float top = __builtin_amdgcn_exp2f(__builtin_fmaf(a.bx, c, a.nm));
     if (a.s == 0.0f && p.prob) {
       // every logit of the row is below kFloor: the sum again, relative to the token drawn
       float s = 0.0f;
@@ -374,11 +384,11 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
       a.s = s;
-      a.m = a.bx;
+      top = 1.0f;
     }
     if (lane == 0) {
       p.token[r] = a.i < p.V ? a.i : 0;  // (no token, no race: only NaN in the row)
-      if (p.prob) p.prob[r] = __builtin_amdgcn_exp2f((a.bx - a.m) * c) / a.s;
+      if (p.prob) p.prob[r] = top / a.s;
     }
   }
 }
@@ -392,9 +402,8 @@ hipError_t launch_token_sample(const SampleArgs& a, hipStream_t stream) {
   p.prob = a.prob;
   p.row_stride_bytes = a.row_stride * (a.bf16 ? 2 : 4);
   p.V = a.V;
-  const float inv_t = 1.0f / a.temperature;
   p.c64 = 1.4426950408889634 / (double)a.temperature;
-  p.inv_t = inv_t < 0x1p127f ? inv_t : 0x1p127f;  // (infinite below T = 2^-128: then 0 / T was NaN)
+  p.c = p.c64 < 0x1p127 ? (float)p.c64 : 0x1p127f;  // (infinite below T = 2^-128: then 0 c was NaN)
   p.k0 = (uint32_t)(a.seed & 0xffffffffu);
   p.k1 = (uint32_t)(a.seed >> 32);
   p.step = a.step;

@@ -149,3 +149,27 @@ def test_sample_repeats_at_near_ties():
                 assert (np.sort(u, 1)[:, -1] == np.sort(u, 1)[:, -2]).any()
                 assert np.array_equal(draws[0], y.argmax(1))
             assert (y.max(1) - y[np.arange(R), draws[0]]).max() <= 1e-6
+
+
+@pytest.mark.parametrize("R,V,dtype", [(400, 32000, "bf16"), (64, 32003, "f32"), (200, 126464, "bf16"), (40, 5, "f32")])
+@pytest.mark.parametrize("T", [0.1, 0.3, 1.0])
+def test_sample_probability_error(R, V, dtype, T):
+    """The probability is a share of the row's sum: not above 1 (a raised token takes nearly all
+    of many of these rows), and within 1.5e-6 of the exact one: 2^-24 |z| ln 2 for the rounding of
+    log2 e / T in the terms beside the maximum (|z| about 20 where a term still counts: 8e-7),
+    two ulp of the exponentials and 2^-23 for the sums of a thread's few chunks and the tree."""
+    announce(f"token sample probability R{R} V{V} {dtype} T{T}")
+    g = torch.Generator().manual_seed(V + R)
+    per = 8 if dtype == "bf16" else 4
+    x = 2.0 * torch.randn(R, (V + per - 1) // per * per, generator=g)
+    top = torch.randint(0, V, (R,), generator=g)
+    x[torch.arange(R), top] += 14.0 * torch.rand(R, generator=g)
+    x = x.to(synth.TORCH_DTYPE[dtype])
+    tok, prob = cover.cover_token_sample(x.cuda()[:, :V], T, 11, 2)
+    torch.cuda.synchronize()
+    assert prob.max().item() <= 1.0
+    z = x[:, :V].double() / float(np.float32(T))
+    want = torch.exp(z[torch.arange(R), tok.cpu().long()] - torch.logsumexp(z, 1))
+    err = ((prob.cpu().double() - want) / want)[want > 1e-3].abs()
+    assert err.max().item() <= 1.5e-6, f"{err.max().item():.2e}"
+    print(f"probability error rms {err.pow(2).mean().sqrt().item():.1e} max {err.max().item():.1e}")
