@@ -199,8 +199,9 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
     float y = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      // (at most 2^127; a NaN, from a row without a bound yet, takes part; below 0 is 0)
-      const float t = fminf(__builtin_fmaf(x[e], c23, k23), 2130706432.0f);
+      // (at most 2^127; a NaN, from a row without a bound yet, takes part; a conversion of less
+      // than 0 is undefined)
+      const float t = fmaxf(fminf(__builtin_fmaf(x[e], c23, k23), 2130706432.0f), 0.0f);
       y = fmaxf(y, __builtin_fmaf(__uint_as_float((uint32_t)t), kLn2Up * kTwo32, (float)rnd[e]));
     }
     const bool in = on && y >= (1.0f - 3.0e-7f) * kTwo32;
