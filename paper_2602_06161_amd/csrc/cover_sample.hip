@@ -19,8 +19,10 @@
 // For flat rows nearly every quad qualifies; then they are raced where they are (the queue
 // would only cost).  The race itself needs neither a logarithm nor an exponential for the
 // tokens that cannot beat the best score so far, which is nearly all.  Measured, 256 rows of
-// 126464 bf16 logits N(0, 2^2) with a raised token, before and after: T = 0.1 38.3 -> 18.3 us,
-// T = 0.3 38.1 -> 22.6, T = 1 38.1 -> 30.6.
+// 126464 bf16 logits N(0, 2^2) with a raised token, against running the generator for every
+// token: T = 0.1 38.3 -> 18.0 us, T = 0.3 38.1 -> 22.4, T = 1 38.1 -> 31.4.  In the last round of
+// loads only what a wave has is worked on (2048 rows of 1000: 21.5 us, 28.5 when the padding
+// was folded and offered like the rest, 18.8 now).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -30,6 +32,10 @@
 namespace cover {
 namespace {
 
+template <int N>
+struct IC {
+  static constexpr int value = N;
+};
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const u32x4 gu32x4;
 
@@ -130,6 +136,21 @@ __device__ __forceinline__ int order_int(float f) {
 }
 __device__ __forceinline__ float order_float(int i) { return __int_as_float(i ^ ((i >> 31) & 0x7fffffff)); }
 
+// the wave's largest value, in every lane (x is never NaN)
+__device__ __forceinline__ float wave_max(float x) {
+  auto step = [&](auto ctrl) __attribute__((always_inline)) {
+    const int v = __float_as_int(x);
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, 0xf, 0xf, false)));
+  };
+  step(IC<0x111>{});  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has the row's
+  step(IC<0x112>{});
+  step(IC<0x114>{});
+  step(IC<0x118>{});
+  step(IC<0x142>{});  // row_bcast 15 and 31: lane 63 has the wave's
+  step(IC<0x143>{});
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
 constexpr int kDense = 48;       // lanes from which a quad is raced in place instead of queued
 constexpr int kQueue = 63 + kDense - 1;  // a wave's queue: up to 63 left over, kDense - 1 pushed
 
@@ -196,25 +217,26 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
     float x[4];
     values(w, x);
     constexpr float kTwo32 = 4294967296.0f, kLn2Up = 0.69322f;
-    float y = 0.0f;
+    constexpr float kIn = (1.0f - 3.0e-7f) * kTwo32;
+    float y[4], top = 0.0f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       // (at most 2^127; a NaN, from a row without a bound yet, takes part; a conversion of less
       // than 0 is undefined)
       const float t = fmaxf(fminf(__builtin_fmaf(x[e], c23, k23), 2130706432.0f), 0.0f);
-      y = fmaxf(y, __builtin_fmaf(__uint_as_float((uint32_t)t), kLn2Up * kTwo32, (float)rnd[e]));
+      y[e] = __builtin_fmaf(__uint_as_float((uint32_t)t), kLn2Up * kTwo32, (float)rnd[e]);
+      top = fmaxf(top, y[e]);
     }
-    const bool in = on && y >= (1.0f - 3.0e-7f) * kTwo32;
+    const bool in = on && top >= kIn;
     if (__builtin_amdgcn_ballot_w64(in) == 0) return;
     if (in) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) race1(x[e], race_e(rnd[e]), 4 * (int)q + e);
+      for (int e = 0; e < 4; ++e)
+        if (y[e] >= kIn) race1(x[e], race_e(rnd[e]), 4 * (int)q + e);
     }
-    float sc = (float)acc.sc;
+    const float sc = (float)acc.sc;
     if (__builtin_amdgcn_ballot_w64(sc > best) == 0) return;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sc = fmaxf(sc, __shfl_xor(sc, o));
-    best = sc;
+    best = wave_max(sc);
     if (lane == 0) atomicMax(&s_best, order_int(best));
     set_bound();
   };
@@ -299,9 +321,22 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
       for (int u = 0; u < kUnroll; ++u)
         if (c0 + u * kThreads >= nfull) cur[u] = (u32x4){kBlank, kBlank, kBlank, kBlank};
     }
+    const int first = __builtin_amdgcn_readfirstlane(c0 - lane);  // (uniform: this wave's first chunk)
     float mx[kUnroll][QPC];
+    if (c0 - tid + kRound <= nfull) {
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) fold(cur[u], mx[u]);
+      for (int u = 0; u < kUnroll; ++u) fold(cur[u], mx[u]);
+    } else {  // the last round: chunks that no lane of the wave has cost nothing
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        if (first + u * kThreads < nfull) {
+          fold(cur[u], mx[u]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < QPC; ++k) mx[u][k] = -INFINITY;
+        }
+      }
+    }
     if (c0 == tid) {  // the first bound of the row: its largest logit so far, with the least u
       float top = -INFINITY;
 #pragma unroll
@@ -309,14 +344,14 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
 #pragma unroll
         for (int k = 0; k < QPC; ++k)
           top = fmaxf(top, mx[u][k]);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+      top = wave_max(top);
       if (lane == 0) atomicMax(&s_best, order_int(top > kFloor ? top * c + kMinAdvantage : -INFINITY));
       __syncthreads();
     }
     see_best();
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
+    for (int u = 0; u < kUnroll; ++u) {
+      if (first + u * kThreads >= nfull) break;
 #pragma unroll
       for (int k = 0; k < QPC; ++k) {
         uint32_t w[W];
@@ -324,6 +359,7 @@ __global__ __launch_bounds__(kThreads, 4) void cover_token_sample_kernel(const S
         for (int e = 0; e < W; ++e) w[e] = cur[u][k * W + e];
         offer((uint32_t)(c0 + u * kThreads) * QPC + k, w, mx[u][k]);
       }
+    }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) cur[u] = nxt[u];
   }
@@ -410,8 +446,8 @@ hipError_t launch_token_sample(const SampleArgs& a, hipStream_t stream) {
   p.step = a.step;
   // Up to one row per CU: 1024 threads.  More rows: 512 threads of the same registers each, so
   // that two rows share a CU (1024 at these registers fill one).  256 rows of 126464, T = 0.3:
-  // 22.6 us with 1024 threads, 25.5 with 512; 512 rows: 43.9 against 37.3; 300 rows of 32000 at
-  // T = 0.2 / 1.0: 17.1 / 25.5 against 13.7 / 20.3.
+  // 22.4 us with 1024 threads, 24.8 with 512; 512 rows: 40.7 against 36.2; 300 rows of 32000 at
+  // T = 0.2 / 1.0: 15.5 / 23.8 against 12.6 / 19.7.
   const dim3 grid((unsigned)a.R);
   if (a.R <= 256) {
     if (a.bf16) hipLaunchKernelGGL((cover_token_sample_kernel<true, 1024, 2>), grid, dim3(1024), 0, stream, p);

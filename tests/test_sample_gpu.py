@@ -173,3 +173,26 @@ def test_sample_probability_error(R, V, dtype, T):
     err = ((prob.cpu().double() - want) / want)[want > 1e-3].abs()
     assert err.max().item() <= 1.5e-6, f"{err.max().item():.2e}"
     print(f"probability error rms {err.pow(2).mean().sqrt().item():.1e} max {err.max().item():.1e}")
+
+
+@pytest.mark.parametrize("R", [5, 260])
+@pytest.mark.parametrize("V,dtype", [(255, "f32"), (257, "f32"), (512, "bf16"), (521, "bf16"), (4104, "bf16"),
+                                     (8196, "f32"), (16385, "bf16"), (32776, "bf16")])
+def test_sample_partial_rounds(R, V, dtype):
+    """Rows whose last round of loads leaves waves, or some of a wave's loads, without a chunk
+    (these do nothing), one chunk past a whole round, and the winner among the last tokens."""
+    announce(f"token sample partial rounds R{R} V{V} {dtype}")
+    rng = np.random.default_rng(V)
+    x = rng.normal(0, 1, (R, V))
+    x[::2, -9:] += 12.0
+    dt = synth.TORCH_DTYPE[dtype]
+    per = 8 if dtype == "bf16" else 4
+    buf = torch.zeros((R, (V + per - 1) // per * per), dtype=dt)
+    buf[:, :V] = torch.from_numpy(x).to(dt)
+    tok, prob = cover.cover_token_sample(buf.cuda()[:, :V], 0.8, 4, 6)
+    torch.cuda.synchronize()
+    rtok, rp, y = oracle.token_sample(buf[:, :V].double().numpy(), np.float32(0.8), 4, 6)
+    tok, prob = tok.cpu().numpy(), prob.cpu().numpy()
+    assert (y.max(1) - y[np.arange(R), tok]).max() <= 1e-6  # the score's error, as above
+    same = tok == rtok
+    assert np.allclose(prob[same], rp[same], rtol=2e-6, atol=1e-7)
