@@ -46,6 +46,7 @@ constexpr int kTokThreads = 1024;
 constexpr int kTokUnroll = 4;  // 16-byte loads in flight per thread (more measured slower)
 constexpr float kLog2e = 1.44269504088896341f;
 constexpr float kLn2 = 0.693147180559945309f;
+constexpr float kFloor = -1.0e30f;  // the lowest reference of a row's sum of exponentials
 
 struct TokParams {
   const char* logits;
@@ -102,8 +103,10 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
     }
   }
   // s sums exp2(x log2 e + nm) with nm = -m log2 e rounded once: every term, rescaling and merge
-  // uses that same rounded reference, and its rounding is taken out of the row's sum at the end
-  float m = -INFINITY, nm = INFINITY, s = 0.0f;
+  // uses that same rounded reference, and its rounding is taken out of the row's sum at the end.
+  // The reference stays at kFloor where only lower logits (-inf, or the type's lowest value, whose
+  // product leaves fp32) have been seen: they add zeros.
+  float m = -INFINITY, nm = -(kFloor * kLog2e), s = 0.0f;
   int cbest = -1;
   auto fold = [&](const float* x, int c) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
 #pragma unroll
     for (int e = 1; e < N; ++e) cm = __builtin_fmaxf(cm, x[e]);
     const float mn = __builtin_fmaxf(m, cm);
-    const float nn = -mn * kLog2e;
+    const float nn = -(__builtin_fmaxf(mn, kFloor) * kLog2e);
     s *= __builtin_amdgcn_exp2f(nn - nm);  // 1 unless the max was raised
     cbest = cm > m ? c : cbest;
     m = mn;
@@ -164,15 +167,13 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
     const float xj = BF ? __uint_as_float((uint32_t)(*(const uint16_t*)(row + (int64_t)j * 2)) << 16)
                         : *(const float*)(row + (int64_t)j * 4);
     if (xj > m) {
-      const float nn = -xj * kLog2e;
-      s = (s == 0.0f ? 0.0f : s * __builtin_amdgcn_exp2f(nn - nm)) + __builtin_amdgcn_exp2f(__builtin_fmaf(xj, kLog2e, nn));
       m = xj;
-      nm = nn;
       ibest = j;
       cbest = -1;
-    } else {
-      s += __builtin_amdgcn_exp2f(__builtin_fmaf(xj, kLog2e, nm));
     }
+    const float nn = -(__builtin_fmaxf(m, kFloor) * kLog2e);
+    s = (s == 0.0f ? 0.0f : s * __builtin_amdgcn_exp2f(nn - nm)) + __builtin_amdgcn_exp2f(__builtin_fmaf(xj, kLog2e, nn));
+    nm = nn;
   }
   // The row's maximum first: then only the threads that hold it read their best chunk again (a
   // line from HBM each: when every thread did, that was a quarter of the logits' bytes), while
@@ -189,8 +190,16 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
   const bool holds = m == M;
   u32x4 best = {};
   if (holds && cbest >= 0) best = chunk(cbest);
-  const float nM = -M * kLog2e;
+  const bool plain = __builtin_fabsf(M) < -kFloor;
+  float nM = -(M * kLog2e);
   float t = s == 0.0f ? 0.0f : s * __builtin_amdgcn_exp2f(nM - nm);
+  if (!plain) {  // no logit above kFloor, or products beyond fp32: the sum again, by differences
+    nM = t = 0.0f;
+    for (int j = tid; j < p.V; j += kTokThreads) {
+      const float xj = BF ? __uint_as_float((uint32_t)((const uint16_t*)row)[j] << 16) : ((const float*)row)[j];
+      t += __builtin_amdgcn_exp2f((xj - M) * kLog2e);
+    }
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
   if (lane == 0) ss[wave] = t;
@@ -214,10 +223,10 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
 #pragma unroll
       for (int w = 0; w < n; ++w) a[w] += a[w + n];
     // the sum is 2^c times that of exp(x - M), c the rounding of nM
-    const float c = __builtin_fmaf(M, kLog2e, nM);
+    const float c = plain ? __builtin_fmaf(M, kLog2e, nM) : 0.0f;
     const float lz = __builtin_fmaf(__builtin_amdgcn_logf(a[0]) - c, kLn2, M);  // natural log-sum-exp
-    if (p.conf) p.conf[r] = __builtin_fmaf(c, kLn2, 1.0f) / a[0];    // exp(max - lz)
-    if (p.argmax) p.argmax[r] = si;
+    if (p.conf) p.conf[r] = __builtin_amdgcn_exp2f(c) / a[0];        // exp(max - lz)
+    if (p.argmax) p.argmax[r] = si < p.V ? si : 0;  // (no number in the row)
     if (p.logp) p.logp[r] = xy - lz;
   }
 }

@@ -106,6 +106,54 @@ def test_token_stats_where_the_maximum_lies(dtype, V):
     np.testing.assert_allclose(cf.cpu().numpy(), torch.exp(xd.max(1).values - lz).numpy(), rtol=TOK_RTOL)
 
 
+@pytest.mark.parametrize("dtype,V", [("bf16", 5), ("f32", 3), ("bf16", 20), ("bf16", 8197), ("f32", 4099), ("f32", 40003)])
+def test_token_stats_masked_and_large_logits(dtype, V):
+    """Logits at the type's lowest value (a masked vocabulary) in whole chunks from the start of
+    the row, in the tail and everywhere but one; -inf in the same places; rows of one huge level;
+    and logits so large that their reference's rounding is no small number.  Finite and exact to
+    the tolerances above, relative to the size of the logits where that is the rounding."""
+    announce(f"token stats masked {dtype} V {V}")
+    dt = synth.TORCH_DTYPE[dtype]
+    per = 8 if dtype == "bf16" else 4
+    low = torch.finfo(dt).min
+    g = torch.Generator().manual_seed(V)
+    x = torch.randn(13, (V + per - 1) // per * per, generator=g) * 2
+    x[0, : V // 2] = low
+    x[1, V // 2:] = low
+    x[2] = low
+    x[2, V // 3] = 1.0
+    x[3] = low                                   # finite: V equal logits
+    x[4, : V // 2] = -torch.inf
+    x[5] = -torch.inf
+    x[5, V - 1] = 0.5
+    x[6] = 3.0e38
+    x[7, V // 2] = 3.0e38
+    x[8] *= 1.0e8                                # the reference's rounding is several units
+    x[9] *= -1.0e5
+    x[10, V - 1] = low
+    x[11, : V - 1] = low
+    x[12] *= -1.0e31
+    x = x.to(dt)
+    tok = torch.full((13,), V - 1, dtype=torch.int32)
+    lg, cf, am = cover.cover_token_stats(x.cuda()[:, :V], tok.cuda())
+    torch.cuda.synchronize()
+    xd = x[:, :V].double()
+    top = xd.max(1).values
+    total = torch.exp(xd - top[:, None]).sum(1)
+    assert torch.equal(am.cpu().long(), (xd == top[:, None]).long().argmax(1))
+    np.testing.assert_allclose(cf.cpu().numpy(), (1 / total).numpy(), rtol=TOK_RTOL)
+    # the log of the sum is rounded to fp32, and so is its difference with a logit of that size
+    want = (xd[:, V - 1] - top - total.log()).numpy()
+    size = np.maximum(top.abs(), xd[:, V - 1].abs()).numpy()
+    got = lg.cpu().numpy().astype(np.float64)
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], np.full(inf.sum(), -np.inf))
+    assert (np.abs(got[~inf] - want[~inf]) <= TOK_ATOL + 2.0**-22 * size[~inf]).all()
+    x[0], x[1] = -torch.inf, torch.nan           # no number in the row: still a token of the vocabulary
+    _, cf, am = cover.cover_token_stats(x.cuda()[:2, :V], want_logp=False)
+    assert torch.equal(am.cpu(), torch.zeros(2, dtype=torch.int32)) and cf.isnan().all().item()
+
+
 def _stats_case(a, r0, masked, drafted):
     t = {k: a[k].cuda() for k in ("q", "k_live", "v_live", "k_cache", "v_cache", "seed_idx", "n_seed")}
     _, lse = cover.cover_attn_fwd(t["q"], t["k_live"], t["v_live"], t["k_cache"], t["v_cache"],
