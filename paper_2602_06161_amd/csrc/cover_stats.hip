@@ -187,7 +187,16 @@ __global__ __launch_bounds__(kTokThreads) void cover_token_stats_kernel(const To
   float M = sm[0];
 #pragma unroll
   for (int w = 1; w < kTokThreads / 64; ++w) M = __builtin_fmaxf(M, sm[w]);
-  const bool holds = m == M;
+  // (of several threads of a wave, on rows with ties, only the one with the smallest index does:
+  // their chunks don't overlap, and a tail element lies behind every chunk)
+  bool holds = m == M;
+  if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(holds)) > 1) {
+    const int key = holds ? (cbest >= 0 ? cbest * N : ibest) : 0x7fffffff;
+    int least = key;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) least = min(least, __shfl_xor(least, off));
+    holds = key == least;
+  }
   u32x4 best = {};
   if (holds && cbest >= 0) best = chunk(cbest);
   const bool plain = __builtin_fabsf(M) < -kFloor;

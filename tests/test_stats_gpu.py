@@ -144,7 +144,7 @@ def test_token_stats_masked_and_large_logits(dtype, V):
     np.testing.assert_allclose(cf.cpu().numpy(), (1 / total).numpy(), rtol=TOK_RTOL)
     # the log of the sum is rounded to fp32, and so is its difference with a logit of that size
     want = (xd[:, V - 1] - top - total.log()).numpy()
-    size = np.maximum(top.abs(), xd[:, V - 1].abs()).numpy()
+    size = torch.maximum(top.abs(), xd[:, V - 1].abs()).numpy()
     got = lg.cpu().numpy().astype(np.float64)
     inf = np.isinf(want)
     assert np.array_equal(got[inf], np.full(inf.sum(), -np.inf))
@@ -152,6 +152,29 @@ def test_token_stats_masked_and_large_logits(dtype, V):
     x[0], x[1] = -torch.inf, torch.nan           # no number in the row: still a token of the vocabulary
     _, cf, am = cover.cover_token_stats(x.cuda()[:2, :V], want_logp=False)
     assert torch.equal(am.cpu(), torch.zeros(2, dtype=torch.int32)) and cf.isnan().all().item()
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 7), ("f32", 6), ("bf16", 523), ("f32", 1030), ("bf16", 16397), ("f32", 8201)])
+def test_token_stats_ties_within_a_wave(dtype, V):
+    """Several threads of one wave hold the row's maximum: neighbouring and distant chunks, a
+    thread's second chunk against another's first, chunks against the tail, whole rows of one
+    level.  The smallest index wins."""
+    announce(f"token stats ties in a wave {dtype} V {V}")
+    t = synth.token_inputs(8, V, seed=V + 1, dtype=dtype)
+    x = t["buffer"]
+    n = 8 if dtype == "bf16" else 4
+    top = x[:, :V].max().item() + 1.0
+    second = 1024 * n
+    ties = [(n + 1, 3 * n), (5 * n + 2, 2 * n + 3, 4 * n), (V - 1, V - 2), (V - 1, n), (second + 2 * n, n + 2),
+            (second + n, 3 * n + 1, V - 1), range(V), range(V // 2, V)]
+    for r, where in enumerate(ties):
+        for j in where:
+            x[r, j % V] = top
+    _, cf, am = cover.cover_token_stats(x.cuda()[:, :V], want_logp=False)
+    torch.cuda.synchronize()
+    xd = x[:, :V].double()
+    assert torch.equal(am.cpu().long(), (xd == xd.max(1, keepdim=True).values).long().argmax(1))
+    np.testing.assert_allclose(cf.cpu().numpy(), torch.exp(xd.max(1).values - torch.logsumexp(xd, 1)).numpy(), rtol=TOK_RTOL)
 
 
 def _stats_case(a, r0, masked, drafted):
