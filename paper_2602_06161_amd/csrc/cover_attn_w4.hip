@@ -35,6 +35,8 @@
 //     A lane's per-stage probability sum above 2^24 (or not finite) flags the workgroup, which
 //     then recomputes its tile with an exact per-stage rescaling pass.  The flag never fires
 //     unless a later score exceeds the first stage's maximum by more than 24 in log2 units.
+//     At D = 64 the rows are rescaled after such a stage, up to 2^64; only beyond is the tile
+//     computed again.
 //   * Waves w and w ^ 2 hold the same queries over the two key halves; they exchange one
 //     32-query tile each through LDS at the end, so each wave finishes 32 complete rows.
 #include <hip/hip_runtime.h>
@@ -600,6 +602,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void cover_attn_w4_kern
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
   // row sums of the bf16 weights (as the MFMA used them) and the range check
+  float stage_sum[2];
   auto rowsums = [&](bf16x8 (*pk)[2]) __attribute__((always_inline)) -> uint64_t {
     uint64_t bad = 0;
 #pragma unroll
@@ -615,9 +618,34 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void cover_attn_w4_kern
       }
       const float st = ls[0] + ls[1];
       lsum[t] += st;
+      stage_sum[t] = st;
       bad |= __builtin_amdgcn_ballot_w64(!(st <= kBig));
     }
     return bad;
+  };
+  // D = 64: after a stage whose sums left the safe range (`over`), their rows' references are raised
+  // to them and O and the sums rescaled; the weights are floating-point numbers, so this stage's
+  // are as exact as others' as long as nothing overflows.  Returns the lanes for which that
+  // cannot be said (2^64 leaves the other half of the exponents to V): the tile is computed again.
+  // At D = 128 every such tile is.  B4 H16 L1001 d64 with the last quarter's scores 4 or 8 times
+  // as large: 41 us with the eight-wave kernel, 54 when every such tile was computed again, 27
+  // here (as without such scores: the test is the one that was there); 16 times, 54.
+  auto raise = [&](uint64_t over) __attribute__((always_inline)) -> uint64_t {
+    if (__builtin_expect(over == 0, 1)) return 0;
+    uint64_t lost = 0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const float st = swap_max(stage_sum[t]);  // (the two lanes of a row keep one reference)
+      lost |= __builtin_amdgcn_ballot_w64(!(st <= kBig * kBig * 65536.0f));
+      const int k = st > kBig ? __builtin_amdgcn_frexp_expf(st) : 0;
+      m[t] += (float)k;
+      lsum[t] = __builtin_amdgcn_ldexpf(lsum[t], -k);
+#pragma unroll
+      for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][db][r] = __builtin_amdgcn_ldexpf(o[t][db][r], -k);
+    }
+    return lost;
   };
   // exp2(c2 s - m) -> bf16 P (both tiles); returns the lanes whose per-stage sum left the
   // safe range
@@ -854,7 +882,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void cover_attn_w4_kern
         load_diag_v();
       }
     }
-    bad |= fused(kbuf((P + 1) % 3), sn, sc, vbuf(P % 3), kbuf(P % 3), kg, vbuf((P + 2) % 3), vg);
+    const uint64_t over = fused(kbuf((P + 1) % 3), sn, sc, vbuf(P % 3), kbuf(P % 3), kg, vbuf((P + 2) % 3), vg);
+    if constexpr (D == 128) bad |= over;
+    else bad |= raise(over);
     ++i;
     return false;
   };
@@ -890,9 +920,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 1 : 2) void cover_attn_w4_kern
     __builtin_amdgcn_s_barrier();
     COVER_TSTAMP(70);
     bf16x8 pk[2][2];
-    bad |= softmax(sc, pk, m);
+    const uint64_t over = softmax(sc, pk, m);
     const int vb = last % 3;
     pv(vbuf(0) + (vb == 0 ? 0 : (vb == 1 ? (int)(vbuf(1) - vbuf(0)) : (int)(vbuf(2) - vbuf(0)))), pk, IC<4>{});
+    if constexpr (D == 128) bad |= over;
+    else bad |= raise(over);
     if (block_seeded) {
       if (diag_lds) diag_from_lds();
       s_live = live_score();

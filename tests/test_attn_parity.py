@@ -158,6 +158,35 @@ def test_bf16_edges_of_both_kernels(d, many, L, n, layout, late):
     check_attn(out, lse, ref, lref, torch.bfloat16, f"d{d} L{L} many {many}")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,n,how", [(1001, 24, "rise"), (1001, 24, "one"), (1024, 0, "fall"), (700, 700, "rise"),
+                                     (640, 130, "first")])
+def test_bf16_scores_outgrow_the_reference(d, L, n, how):
+    """Scores that rise from stage to stage by more than the reference maximum tolerates, in every
+    row or in one head's last stages only, or fall; every position a seed (the cached diagonal,
+    which must not move the reference, the largest score); and a first stage far below the rest."""
+    announce(f"bf16 d{d} L{L} seeds{n} scores {how}")
+    a = _custom(L, 1, 16, 4, L, d, n)
+    up = torch.linspace(0, 40, L)[:, None]
+    lift = {"rise": up, "fall": up.flip(0), "one": torch.where(up > 35, 30.0, 0.0),
+            "first": torch.where(torch.arange(L)[:, None] < 64, -80.0, 0.0)}[how]
+    direction = torch.nn.functional.normalize(torch.ones(d), dim=0)
+    heads = slice(0, 1) if how == "one" else slice(None)
+    for k in ("k_live", "k_cache"):
+        a[k] = a[k].float()
+        a[k][:, heads] += lift * direction * d ** 0.5 / 4
+        a[k] = a[k].bfloat16()
+    a["q"] = (a["q"].float() * 0.5 + 4 * direction).bfloat16()
+    if n == L:  # a seed's own cached key, which its row does not see, above everything else
+        a["k_cache"] = (a["k_cache"].float() + 3 * direction).bfloat16()
+    out, lse = _run(a)
+    ref, lref = _oracle(a)
+    # the lse of scores in the hundreds: bf16 scores' fp32 sums, 2^-22 of their size on top
+    check_attn(out, None, ref, None, torch.bfloat16, f"d{d} {how}")
+    err = np.abs(lse.double().cpu().numpy().reshape(lref.shape) - lref)
+    assert (err <= 2e-2 + 2.0**-20 * np.abs(lref)).all()
+
+
 def test_zero_seeds_and_no_seed_arrays():
     announce("bf16 zero seeds / max_seeds 0")
     a = _custom(5, 1, 4, 2, 200, 128, 6)
