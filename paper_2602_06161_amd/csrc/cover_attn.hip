@@ -13,8 +13,8 @@
 //
 // On the fp32 matrix instruction
 // (v_mfma_f32_16x16x4_f32: fp32 operands, products and sums).  One workgroup of up to 8 waves
-// per 16 query rows of one (b, h); the waves take the 16-key tiles in turn and merge their
-// (max, sum, O) through LDS.  The calls are small (a layer of tens to hundreds of tokens), so
+// (one, where there are enough) per 16 query rows of one (b, h); the waves take the 16-key tiles in
+// turn and merge their (max, sum, O) through LDS.  The calls are small (a layer of tens to hundreds of tokens), so
 // what bounds them is latency: 16-row tiles give the most workgroups and the shortest chain per
 // tile (1024 matrix cycles at d = 64), each wave requests its next tile before it works on one,
 // and every operand is read from memory in the layout the instruction wants, without LDS:
@@ -70,11 +70,12 @@ struct ParamsF {
 constexpr int kFWaves = 8;  // most waves per workgroup
 constexpr int kFT = 16;     // queries per workgroup, keys per tile
 
-template <int D>
-__global__ __launch_bounds__(64 * kFWaves) void cover_attn_f32_kernel(const ParamsF p) {
+// WAVES: the most of a workgroup, which size its LDS
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void cover_attn_f32_kernel(const ParamsF p) {
   constexpr int KS = D / 16, DC = D / 64;
-  __shared__ __attribute__((aligned(16))) float sO[kFWaves][kFT][D + 4];
-  __shared__ float sM[kFWaves][kFT], sL[kFWaves][kFT];
+  __shared__ __attribute__((aligned(16))) float sO[WAVES][kFT][D + 4];
+  __shared__ float sM[WAVES][kFT], sL[WAVES][kFT];
   __shared__ uint32_t bits[COVER_MAX_L / 32];
   const int tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, nw = nth >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -255,14 +256,23 @@ hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream) {
   p.q_sb = a.q_sb; p.q_sh = a.q_sh; p.q_sl = a.q_sl;
   p.kv_sb = a.kv_sb; p.kv_sh = a.kv_sh; p.kv_sl = a.kv_sl;
   p.n_wg = (int64_t)a.B * a.Hq * p.n_qt;
-  // a wave per key tile up to 8; past 2^20 tiles of queries a workgroup takes several
-  const int nw = (a.L + kFT - 1) / kFT;
-  const dim3 block(64u * (unsigned)(nw < kFWaves ? nw : kFWaves));
+  // Few query tiles: a wave per key tile up to 8, for the shortest chain.  From 2048 query tiles
+  // the chip is full of them, and one wave that walks all keys saves the merge and LDS (43 KB at
+  // d = 64: three workgroups per CU): us with 8 waves and with 1, d64: 128 heads of L 256 62 / 40,
+  // 2048 of L 65 197 / 72 (192 with a lane per query row), 32 of L 256 (512 tiles) 17 / 26; d128,
+  // 2048 heads of L 100 468 / 297.  Not at d = 128 past 640 keys (128 heads of L 1024 990 / 1058),
+  // where one wave's next tile arrives late.  Past 2^20 query tiles a workgroup takes several.
+  const int n_kt = (a.L + kFT - 1) / kFT;
+  const int nw = p.n_wg >= 2048 && (a.d == 64 || n_kt <= 40) ? 1 : (n_kt < kFWaves ? n_kt : kFWaves);
+  const dim3 block(64u * (unsigned)nw);
   const dim3 grid((unsigned)(p.n_wg < (1 << 20) ? p.n_wg : (1 << 20)));
-  if (a.d == 128)
-    hipLaunchKernelGGL(cover_attn_f32_kernel<128>, grid, block, 0, stream, p);
-  else
-    hipLaunchKernelGGL(cover_attn_f32_kernel<64>, grid, block, 0, stream, p);
+  if (a.d == 128) {
+    if (nw == 1) hipLaunchKernelGGL((cover_attn_f32_kernel<128, 1>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((cover_attn_f32_kernel<128, kFWaves>), grid, block, 0, stream, p);
+  } else {
+    if (nw == 1) hipLaunchKernelGGL((cover_attn_f32_kernel<64, 1>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((cover_attn_f32_kernel<64, kFWaves>), grid, block, 0, stream, p);
+  }
   return hipGetLastError();
 }
 

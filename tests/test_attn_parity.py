@@ -78,6 +78,17 @@ def test_f32_tile_edges(L, d, n):
     check_attn(out, lse, ref, lref, torch.float32, f"L{L} d{d}")
 
 
+@pytest.mark.parametrize("B,L,d,n", [(43, 33, 64, 3), (33, 49, 128, 9), (64, 17, 64, 17), (8, 250, 64, 30)])
+def test_f32_one_wave_per_workgroup(B, L, d, n):
+    """From 2048 query tiles on one wave walks all key tiles: whole and ragged, seeds in any."""
+    announce(f"fp32 one wave B{B} L{L} d{d} seeds{n}")
+    a = _custom(L + d, B, 16, 4, L, d, n, dtype="f32")
+    assert B * 16 * -(-L // 16) >= 2048
+    out, lse = _run(a)
+    ref, lref = _oracle(a)
+    check_attn(out, lse, ref, lref, torch.float32, f"B{B} L{L} d{d}")
+
+
 def test_f32_more_tiles_than_workgroups():
     """Past 2^20 query tiles a workgroup takes several: one-token sequences, whose output is
     their own value row."""
