@@ -292,9 +292,9 @@ cover_status cover_attn_stats_noalloc(const void* q, const void* k_live, const v
  *   q_off, Lq   0 <= q_off, 0 <= Lq, q_off + Lq <= attn.L (Lq == 0 is a no-op)
  *   n_split     1 <= n_split <= 256.  1: one launch, one workgroup per 32 query rows whose
  *               waves split the keys among themselves (no workspace).  > 1: the keys are cut
- *               into n_split ranges processed by separate workgroups and merged by a second
- *               launch (more workgroups per query row; the partial results go through the
- *               workspace)
+ *               into at most n_split ranges (fewer where those finish sooner, one included)
+ *               processed by separate workgroups and merged by a second launch (more
+ *               workgroups per query row; the partial results go through the workspace)
  */
 typedef struct {
   cover_attn_desc attn;
@@ -321,8 +321,9 @@ typedef struct {
  * contiguous (may be NULL); workspace: for n_split > 1 a device fp32 buffer of
  * COVER_ATTN_RECT_WORKSPACE(B, Hq, Lq, n_split) floats owned by the caller (contents on
  * entry ignored, on exit unspecified); for n_split == 1 not used (may be NULL).  One kernel
- * launch on `stream` for n_split == 1, two otherwise (partial results per key split, then
- * a merge); every sum runs in a fixed order, so results are deterministic.
+ * launch on `stream` for one range of the keys, two otherwise (partial results per range, then
+ * a merge; past 2^23 workgroups the first in several); every sum runs in a fixed order, so
+ * results are deterministic.
  * Returns COVER_ERR_UNSUPPORTED for a dtype other than bf16, d != 128, L > COVER_MAX_L, or
  * n_split == 1 with kv_sl >= 2^26.
  */

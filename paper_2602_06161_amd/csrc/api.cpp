@@ -301,8 +301,9 @@ cover_status cover_attn_rect(const void* q, const void* k_live, const void* v_li
   if (lse && !aligned(lse, 4)) return COVER_ERR_INVALID;
   if (n_split > 1 && (!workspace || !aligned(workspace, 16))) return COVER_ERR_INVALID;
   if (n_split == 1 && D.kv_sl >= (int64_t(1) << 26)) return COVER_ERR_UNSUPPORTED;
-  // grids: at most 2^32 work-items per launch (512 per workgroup for n_split == 1; 256 for the
-  // split kernel, and one 64-lane wave per row for the merge)
+  // grids: at most 2^32 work-items per launch.  n_split == 1: 512 per workgroup.  n_split > 1: the
+  // first kernel is launched in chunks of that size, its workgroups counted in 31 bits (at most 4
+  // per 128 rows and range), and the merge has one 64-lane wave per row
   if (n_split == 1 && (int64_t)D.B * D.Hq * ((Lq + 31) / 32) > (int64_t(1) << 23) - 8)
     return COVER_ERR_UNSUPPORTED;
   if (n_split > 1 && ((int64_t)D.B * D.Hq * ((Lq + 127) / 128) * n_split > (int64_t(1) << 24) - 1 ||

@@ -638,6 +638,32 @@ bool attn_small(const AttnArgs& a) {
          a.kv_sl < (int64_t(1) << 26);
 }
 
+// The key ranges a call with n_split of them uses: all, unless fewer finish sooner.  A tile of 32
+// query rows reads its range of the keys for itself, so splitting past the point where the
+// workgroups fill the chip only adds rounds and records.  Cost in 32-key stages, as measured: rounds
+// of 256 workgroups, each as long as its stages and 18 more for its start and merge; 24 for the
+// second launch.  Asked for 64 ranges at B1 Hq32 L8192, 64 rows: 100 us with all of them, 57 on the
+// former kernel of 4 waves per 128 rows, 21.8 with the 4 that this picks; 4 ranges at B1 Hq32 L1024, 256
+// rows: 34, 23.3, 12.1 with one.
+static int rect_ranges(int64_t tiles, int stages, int n_split, bool whole) {
+  int best = n_split;
+  int64_t least = INT64_MAX;
+  auto offer = [&](int64_t n) {
+    if (n < (whole ? 1 : 2) || n > n_split) return;
+    const int length = (int)((stages + n - 1) / n);
+    const int64_t cost = (tiles * n + 255) / 256 * (length + 18) + (n > 1 ? 24 : 0);
+    if (cost < least) {
+      best = (int)n;
+      least = cost;
+    }
+  };
+  offer(n_split);
+  for (int rounds = 1; rounds <= 8; ++rounds) offer(256 * rounds / tiles);
+  offer(2);
+  offer(1);
+  return best;
+}
+
 hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
   RectParams p;
   p.q = (const __bf16*)a.q; p.kl = (const __bf16*)a.k_live; p.vl = (const __bf16*)a.v_live;
@@ -647,16 +673,18 @@ hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
   p.B = a.B; p.Hq = a.Hq; p.Hkv = a.Hkv; p.L = a.L; p.Lq = a.Lq; p.q_off = a.q_off;
   p.max_seeds = a.max_seeds; p.group = a.Hq / a.Hkv;
   p.n_qt = (a.Lq + kTQ - 1) / kTQ;
-  p.n_split = a.n_split;
   const int stages = (a.L + kStage - 1) / kStage;
-  p.split_stages = (stages + a.n_split - 1) / a.n_split;
+  const int64_t tiles = (int64_t)a.B * a.Hq * p.n_qt;
+  constexpr int64_t kMaxGrid = (int64_t(1) << 23) - 8;  // workgroups per launch: under 2^32 work-items
+  p.wide = a.kv_sl >= (int64_t(1) << 26);
+  p.n_split = rect_ranges(tiles, stages, a.n_split, !p.wide && tiles <= kMaxGrid);
+  p.split_stages = (stages + p.n_split - 1) / p.n_split;
   p.c2 = a.scale * 1.44269504088896341f;
   p.q_sb = a.q_sb; p.q_sh = a.q_sh; p.q_sl = a.q_sl;
   p.kv_sb = a.kv_sb; p.kv_sh = a.kv_sh; p.kv_sl = a.kv_sl;
-  p.wide = a.kv_sl >= (int64_t(1) << 26);
-  const int64_t n = (int64_t)a.B * a.Hq * p.n_qt * a.n_split;
+  const int64_t n = tiles * p.n_split;
   const dim3 block(64 * kTW);
-  if (a.n_split == 1) {
+  if (p.n_split == 1) {
     p.n_wg = (int)n;
     p.xcd_slots = (int)((n + 7) / 8);
     const dim3 grid((unsigned)(8 * (int64_t)p.xcd_slots));
@@ -664,7 +692,6 @@ hipError_t launch_attn_rect(const RectArgs& a, hipStream_t stream) {
     else hipLaunchKernelGGL((cover_attn_tile_kernel<64, false>), grid, block, 0, stream, p);
     return hipGetLastError();
   }
-  constexpr int64_t kMaxGrid = (int64_t(1) << 23) - 8;  // workgroups per launch: under 2^32 work-items
   for (int64_t first = 0; first < n; first += kMaxGrid) {
     p.first_wg = (int)first;
     p.n_wg = (int)(n - first < kMaxGrid ? n - first : kMaxGrid);

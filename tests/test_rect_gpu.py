@@ -178,3 +178,63 @@ def test_distinct_seed_lists_per_batch_row(n_split):
                                a["n_seed"], scale=a["scale"], mode="fast", rows=rows)
     check_attn(out, lse, ref_o.reshape(B, Hq, Lq, d), ref_l.reshape(B, Hq, Lq), torch.bfloat16,
                "distinct seeds")
+
+
+@pytest.mark.parametrize("L,Lq,q_off,n_split,pos", [
+    (2100, 77, 2023, 4, [0, 31, 32, 525, 1056, 2023, 2050, 2099]),     # the last range's last stage ragged
+    (2100, 33, 700, 40, [699, 700, 710, 732, 2099]),                   # ranges without keys
+    (2048, 8, 2040, 2, list(range(0, 2048, 3))),                       # a long seed list, every stage patched
+    (3000, 1, 1500, 11, [1500]),                                       # one row, a seed
+    (2500, 64, 0, 7, list(range(2500))),                               # every position a seed
+    (5000, 100, 4000, 256, [4000 + 5 * i for i in range(20)])])
+def test_split_form(L, Lq, q_off, n_split, pos):
+    """Key ranges in separate workgroups and the merge, at shapes where the call uses the ranges
+    it is given (from 48 stages of 32 keys two beat one), against the oracle and bit for bit
+    against a second call."""
+    a = _custom(L + n_split, 1, 2, 1, L, 0, positions=pos)
+    out, lse = _check(a, q_off, Lq, n_split=n_split, where="split form")
+    out2, lse2 = _check(a, q_off, Lq, n_split=n_split, where="split form again")
+    assert torch.equal(out, out2) and torch.equal(lse, lse2)
+
+
+@pytest.mark.parametrize("B,Hq,L,Lq,n_split", [(1, 32, 2100, 64, 64), (2, 28, 1000, 100, 8), (4, 32, 700, 70, 3)])
+def test_more_ranges_than_pay(B, Hq, L, Lq, n_split):
+    """Calls that ask for more key ranges than finish soonest use fewer: same rows, and nothing
+    outside the workspace they were given."""
+    a = _custom(B + L, B, Hq, Hq // 4, L, 9)
+    q, kl, vl, kc, vc, si, ns = to_dev(a)
+    need = cover.rect_workspace(B, Hq, Lq, n_split)
+    ws = torch.full((need + 4096,), 7.0, device="cuda")
+    qb = q[:, :, L - Lq:].contiguous()
+    announce(f"rect ranges B{B} Hq{Hq} L{L} Lq{Lq} n_split={n_split}")
+    out, lse = cover.cover_attn_rect(qb, kl, vl, kc, vc, L - Lq, si, ns, n_split=n_split, workspace=ws[:need])
+    one, one_lse = cover.cover_attn_rect(qb, kl, vl, kc, vc, L - Lq, si, ns, n_split=1)
+    torch.cuda.synchronize()
+    assert (ws[need:] == 7.0).all()
+    # both round the same softmax to bf16 in their own order: 2^-8 of an output of up to 4
+    assert (out.float() - one.float()).abs().max().item() < 2e-2
+    assert (lse - one_lse).abs().max().item() < 1e-2
+
+
+def test_rows_further_apart_than_32_bit_offsets():
+    """Key rows 2^26 elements apart (the four K/V tensors interleaved in one buffer), with the key
+    ranges that such strides need."""
+    B, Hq, Hkv, L, Lq, d, gap = 1, 4, 2, 40, 20, 128, 1 << 26
+    g = torch.Generator(device="cuda").manual_seed(4)
+    buf = torch.empty((L - 1) * gap + 8 * d, device="cuda", dtype=torch.bfloat16)
+    views = [torch.as_strided(buf, (B, Hkv, L, d), (0, d, gap, 1), 2 * d * i) for i in range(4)]
+    plain = [torch.randn(B, Hkv, L, d, generator=g, device="cuda").bfloat16() for _ in range(4)]
+    for v, p in zip(views, plain):
+        v.copy_(p)
+    q = torch.randn(B, Hq, Lq, d, generator=g, device="cuda").bfloat16()
+    si = torch.tensor([[3, 25, 31, 32, 39]], device="cuda", dtype=torch.int32)
+    ns = torch.tensor([5], device="cuda", dtype=torch.int32)
+    for n_split in (2, 3):
+        announce(f"rect wide rows n_split={n_split}")
+        out, lse = cover.cover_attn_rect(q, views[0], views[1], views[2], views[3], 20, si, ns, n_split=n_split)
+        want, want_lse = cover.cover_attn_rect(q, *plain, 20, si, ns, n_split=1)
+        torch.cuda.synchronize()
+        assert (out.float() - want.float()).abs().max().item() < 2e-2  # as above
+        assert (lse - want_lse).abs().max().item() < 1e-2
+    del buf, views
+    torch.cuda.empty_cache()
