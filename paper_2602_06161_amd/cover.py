@@ -253,8 +253,8 @@ def rect_splits(B: int, Hq: int, Lq: int, L: int) -> int:
     """Key splits.  1 (the single launch: one workgroup per 32 query rows, its waves split the
     keys) unless the sequence is long and the block leaves most CUs idle: that kernel reads
     all of a head's K and V through one CU per 32 rows, about 100 GB/s per CU, so past 2048
-    keys with fewer than 256 workgroups the keys are split across workgroups instead (about
-    256 workgroups of at least 128 keys each, merged by a second launch)."""
+    keys with fewer than 256 workgroups the keys are split across workgroups instead (1 to 8
+    rounds of 256 workgroups of at least 128 keys each, merged by a second launch)."""
     if L <= 2048 or B * Hq * ((Lq + 31) // 32) >= 256:
         return 1
     tiles, stages = B * Hq * ((Lq + 31) // 32), -(-L // 32)
@@ -270,6 +270,16 @@ def rect_splits(B: int, Hq: int, Lq: int, L: int) -> int:
             if cost < least:
                 best, least = n, cost
     return best
+
+
+def _rect_plan(B: int, Hq: int, Lq: int, L: int, n_split, workspace):
+    """(n_split, floats of workspace) of a call; without an n_split of the caller's as many splits
+    as rect_splits says, or as a smaller workspace of the caller's holds (two at least)."""
+    if n_split is None:
+        n_split = rect_splits(B, Hq, Lq, L)
+        if workspace is not None and n_split > 2:
+            n_split = min(n_split, max(2, workspace.numel() // (B * Hq * Lq * COVER_RECT_RECORD)))
+    return n_split, rect_workspace(B, Hq, Lq, n_split)
 
 
 def cover_attn_rect(q, k_live, v_live, k_cache, v_cache, q_off: int, seed_idx=None, n_seed=None,
@@ -295,9 +305,7 @@ def cover_attn_rect(q, k_live, v_live, k_cache, v_cache, q_off: int, seed_idx=No
         raise ValueError("out must match q's shape, strides and dtype")
     if lse is None and want_lse:
         lse = torch.empty((B, Hq, Lq), device=q.device, dtype=torch.float32)
-    if n_split is None:
-        n_split = rect_splits(B, Hq, Lq, L)
-    need = rect_workspace(B, Hq, Lq, n_split)
+    n_split, need = _rect_plan(B, Hq, Lq, L, n_split, workspace)
     if need == 0:
         workspace = None  # not used by the single launch
     elif workspace is None:
@@ -571,9 +579,7 @@ class PreparedRect:
                  stream=None):
         B, Hq, Lq, d = q.shape
         L = k_live.shape[2]
-        if n_split is None:
-            n_split = rect_splits(B, Hq, Lq, L)
-        need = rect_workspace(B, Hq, Lq, n_split)
+        n_split, need = _rect_plan(B, Hq, Lq, L, n_split, workspace)
         if need and workspace is None:
             workspace = torch.empty(need, device=q.device, dtype=torch.float32)
         self.out, self.lse = cover_attn_rect(q, k_live, v_live, k_cache, v_cache, q_off, seed_idx,

@@ -297,6 +297,25 @@ def test_token_sample_rejects_bad_arguments():
     assert call(cover.TokenDesc(0, 1000, cover.COVER_BF16, 1008), logits=None, tok=None) == cover.COVER_OK
 
 
+def test_rect_plan_fits_a_given_workspace():
+    # a workspace for the splits of the workgroups of 128 rows that 256 hold (5 here) is enough,
+    # also where rect_splits would take more; one that holds fewer than two is refused
+    import torch
+
+    B, Hq, Lq, L = 2, 28, 8, 32768
+    assert cover.rect_splits(B, Hq, Lq, L) > 5
+    record = B * Hq * Lq * cover.COVER_RECT_RECORD
+    assert cover._rect_plan(B, Hq, Lq, L, None, torch.empty(5 * record)) == (5, 5 * record)
+    assert cover._rect_plan(B, Hq, Lq, L, None, torch.empty(6 * record - 1)) == (5, 5 * record)
+    assert cover._rect_plan(B, Hq, Lq, L, None, torch.empty(100 * record))[0] == cover.rect_splits(B, Hq, Lq, L)
+    assert cover._rect_plan(B, Hq, Lq, L, None, None)[0] == cover.rect_splits(B, Hq, Lq, L)
+    assert cover._rect_plan(B, Hq, Lq, L, 7, torch.empty(record)) == (7, 7 * record)  # the caller's own: checked
+    assert cover._rect_plan(B, Hq, Lq, L, None, torch.empty(record)) == (2, 2 * record)
+    q, k = torch.zeros(B, Hq, Lq, 128).bfloat16(), torch.zeros(B, 1, L, 128).bfloat16()
+    with pytest.raises(ValueError):
+        cover.cover_attn_rect(q, k, k, k, k, 0, workspace=torch.empty(2 * record - 1))
+
+
 def test_rect_split_choice():
     # the single launch up to L = 2048, and past it whenever its workgroups fill the GPU
     assert cover.rect_splits(1, 32, 256, 1024) == 1

@@ -216,6 +216,25 @@ def test_more_ranges_than_pay(B, Hq, L, Lq, n_split):
     assert (lse - one_lse).abs().max().item() < 1e-2
 
 
+def test_workspace_smaller_than_the_default_splits():
+    """A workspace of the caller's that holds fewer splits than rect_splits picks, as a plain call
+    and with the arguments marshalled once."""
+    B, Hq, Hkv, L, Lq = 2, 28, 4, 32768, 8
+    announce("rect small workspace")
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q = torch.randn(B, Hq, Lq, 128, generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn(B, Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    ws = torch.full((cover.rect_workspace(B, Hq, Lq, 5) + 1024,), 7.0, device="cuda")
+    out, lse = cover.cover_attn_rect(q, k, v, k, v, L - Lq, workspace=ws[:-1024])
+    p = cover.PreparedRect(q, k, v, k, v, L - Lq, workspace=ws[:-1024])
+    p()
+    one, one_lse = cover.cover_attn_rect(q, k, v, k, v, L - Lq, n_split=1)
+    torch.cuda.synchronize()
+    assert p.n_split == 5 and torch.equal(p.out, out) and (ws[-1024:] == 7.0).all()
+    assert (out.float() - one.float()).abs().max().item() < 2e-2  # as above
+    assert (lse - one_lse).abs().max().item() < 1e-2
+
+
 def test_rows_further_apart_than_32_bit_offsets():
     """Key rows 2^26 elements apart (the four K/V tensors interleaved in one buffer), with the key
     ranges that such strides need."""
