@@ -181,11 +181,13 @@ typedef struct {
  *   logp[r]   = x_r[tokens[r]] - lz_r
  *   conf[r]   = exp(max_v x_r[v] - lz_r)
  *   argmax[r] = the smallest v attaining max_v x_r[v]
- * Arithmetic in fp32 (exp/log of the exp2/log2 units); one pass over the logits.
+ * Arithmetic in fp32 (exp/log of the exp2/log2 units); one pass over the logits (a second over
+ * rows whose maximum is beyond 1e30 in size).
  * Arguments: logits [R, row_stride] (device); tokens int32 [R] (device; may be NULL when
  * logp is NULL); logp, conf fp32 [R] and argmax int32 [R] (device outputs, each may be
  * NULL).  Device-data contract: tokens in [0, V) (a token outside gives logp = NaN, never
- * an out-of-bounds read); logits finite.
+ * an out-of-bounds read); logits finite or -inf (a masked token).  argmax is in [0, V) whatever
+ * the row holds.
  */
 cover_status cover_token_stats(const void* logits, const int32_t* tokens,
                                float* logp, float* conf, int32_t* argmax,
@@ -201,8 +203,10 @@ cover_status cover_token_stats(const void* logits, const int32_t* tokens,
  *              threshold; may be NULL)
  * u_v = ((w >> 9) + 1/2) 2^-23 with w word v % 4 of Philox4x32-10 (Salmon et al., SC 2011)
  * at counter (v / 4, r, step, 0) and key (seed mod 2^32, seed >> 32): a fixed function of
- * (seed, step, row, token), reproducible across launches and devices.  Arithmetic in fp32.
- * temperature: > 0 and finite.  token int32 [R], prob fp32 [R]: device outputs.
+ * (seed, step, row, token), reproducible across launches and devices.  x_v / T + g_v is
+ * compared in fp64 (with g_v from fp32 logarithms), softmax(x / T) summed in fp32.  temperature:
+ * > 0 and finite.  Logits finite or -inf; token is in [0, V) whatever the row holds.  token int32
+ * [R], prob fp32 [R]: device outputs.
  */
 cover_status cover_token_sample(const void* logits, float temperature, uint64_t seed, uint32_t step,
                                 int32_t* token, float* prob, const cover_token_desc* desc,
@@ -221,7 +225,7 @@ typedef struct {
 /* Largest response region cover_attn_stats accepts. */
 #define COVER_STATS_MAX_LR 2048
 /* An upper bound of the workspace of cover_attn_stats in floats, valid for every launch:
- * B * Hq * (1 + ceil(Lr / 32)) * Lr.  cover_attn_stats_workspace gives the exact need. */
+ * B * Hq * (1 + ceil(Lr / 32)) * Lr.  cover_attn_stats_workspace gives what a call asks for. */
 #define COVER_ATTN_STATS_WORKSPACE(B, Hq, Lr) \
   ((int64_t)(B) * (Hq) * (1 + ((int64_t)(Lr) + 31) / 32) * (Lr))
 
@@ -254,8 +258,9 @@ cover_status cover_attn_stats(const void* q, const void* k_live, const void* k_c
 
 /*
  * cover_attn_stats_workspace -- floats of workspace a cover_attn_stats call with these B, Hq
- * and Lr uses: B * Hq * (1 + G) * Lr, with G the number of key groups the launch splits the
- * region's 32-key tiles into (about 256 workgroups in all; G <= ceil(Lr / 32)).  A host
+ * and Lr asks for: B * Hq * (1 + G) * Lr, with G the number of workgroups per head that the
+ * launch divides the region's 32-position tiles among (about 256 workgroups in all; G <=
+ * ceil(Lr / 32)).  The kernels use at most that, now two rows of Lr floats per head.  A host
  * function: no GPU work.  Returns -1 for negative arguments.
  */
 int64_t cover_attn_stats_workspace(int32_t B, int32_t Hq, int32_t Lr);

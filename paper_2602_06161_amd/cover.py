@@ -74,7 +74,7 @@ class StatsDesc(ctypes.Structure):
 
 
 def attn_stats_workspace(B: int, Hq: int, Lr: int) -> int:
-    """Floats of workspace a cover_attn_stats call of this size uses (the library's
+    """Floats of workspace a cover_attn_stats call of this size asks for (the library's
     cover_attn_stats_workspace)."""
     n = lib().cover_attn_stats_workspace(int(B), int(Hq), int(Lr))
     if n < 0:

@@ -20,7 +20,7 @@
 //     split that holds the position.  Then one wave per query row merges the splits and writes O
 //     and the lse.  Against a kernel of 4 waves per 128 query rows that loaded 128 keys, waited,
 //     computed and loaded again (half its waves idle at 64 rows): B1 Hq32/Hkv8 L8192, 64 rows,
-//     38.3 -> 22.4 us; L16000, 8 rows, 62 -> 21; B1 H12 L12000, 180 rows, 56 -> 32.
+//     38.4 -> 21.7 us; L16000, 8 rows, 62 -> 21; B1 H12 L12000, 180 rows, 56 -> 32.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -417,7 +417,8 @@ __global__ __launch_bounds__(64 * kTW, 1) void cover_attn_tile_kernel(const Rect
     vd = *(const raw_t*)(p.vl + ro);
   }
 
-  // V^T operand addresses (as in the split kernel)
+  // V^T operand addresses: lane (G = lane / 16, i = lane % 16) reads keys {0..3, 8..11} + 4 (G / 2)
+  // of d-block db, the key order of the S^T registers
   uint32_t vaddr[D / 32];
   {
     const int G = lane >> 4, ii = lane & 15;

@@ -22,7 +22,7 @@
 //     MFMAs: there a 64-key stage has 512 cycles of MFMA work per SIMD and about as much of
 //     softmax, and a single wave cannot hide one behind the other.  Against a kernel of eight
 //     waves with one 32-query tile each (every operand read from LDS feeding one MFMA), B4 H16
-//     L1001 d64, 24 seeds: 39.5 -> 27.2 us (1.85k cycles per pair of stages).
+//     L1001 d64, 24 seeds: 39.1 -> 25.5 us (1.85k cycles per pair of stages).
 //   * Every global load goes straight to LDS (global_load_lds_dwordx4): the seed list, Q (read
 //     into registers once), the live rows of a seeded tile's diagonal (with the last step, into
 //     the Q area), and K/V stages in three buffers each, issued two stages ahead and

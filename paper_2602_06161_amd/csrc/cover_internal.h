@@ -111,8 +111,9 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
 hipError_t launch_token_stats(const TokenArgs& a, hipStream_t stream);
 hipError_t launch_token_sample(const SampleArgs& a, hipStream_t stream);
 hipError_t launch_attn_stats(const StatsArgs& a, hipStream_t stream);
-// key groups of the attention-mass launch (32-key tiles per group, groups) and the workspace
-// floats that launch uses
+// workgroups per head of the attention-mass launch (32-position tiles per workgroup, workgroups),
+// and the workspace floats a caller of that launch provides: 1 + workgroups rows per head, of which
+// the launch uses two, d_in and d_out (the size callers have been told to provide is kept)
 void stats_key_groups(int B, int Hq, int Lr, int* tpg, int* kg);
 int64_t stats_workspace_floats(int B, int Hq, int Lr);
 // device address of the attention-mass kernels' own static scratch array on the current GPU

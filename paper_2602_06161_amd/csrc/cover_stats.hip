@@ -5,10 +5,10 @@
 // confidence of Sec. 3) and the token attaining it.  One workgroup of 1024 threads per row;
 // each thread streams 16-byte chunks with four loads in flight and keeps an online (max, sum
 // of exp) pair and the chunk where its max was last raised, merged across the workgroup; the
-// index inside that chunk is found at the end, by the threads that hold the row's maximum.  The
-// placed token and its logit are fetched at the start by scalar loads.  HBM bounds it: 256 rows of
-// 126464 bf16 logits (65 MB) 13.2 us, 15.0 when every thread read its best chunk again (a line
-// from memory each, a quarter of the logits' bytes); 512 rows, cold, 29.1 -> 25.4.
+// index inside that chunk is found at the end, by one thread of each wave that holds the row's
+// maximum.  The placed token and its logit are fetched at the start by scalar loads.  HBM bounds
+// it: 256 rows of 126464 bf16 logits (65 MB) 13.3 us, 15.0 when every thread read its best chunk
+// again (a line from memory each, a quarter of the logits' bytes); 512 rows, cold, 29.1 -> 25.4.
 //
 // cover_attn_stats_kernel + cover_attn_stats_reduce_kernel: the in/out attention masses of
 // Sec. 5.3 over a response region [r0, r0+Lr), from the last layer's corrected weights
