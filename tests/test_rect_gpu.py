@@ -59,7 +59,8 @@ def test_small_blocks(q_off, Lq):
 
 @pytest.mark.parametrize("n_split", [1, 3, 7, 32, 40])
 def test_split_counts(n_split):
-    # 40 splits of a 32-stage sequence leave splits without keys
+    # asked for; at 32 stages the launch uses one range whatever it is given (test_split_form has
+    # shapes that use theirs, also with ranges without keys)
     a = synth.attn_inputs("llada", seed=2)
     _check(a, 768, 256, n_split=n_split, where="splits")
 
@@ -195,6 +196,30 @@ def test_split_form(L, Lq, q_off, n_split, pos):
     out, lse = _check(a, q_off, Lq, n_split=n_split, where="split form")
     out2, lse2 = _check(a, q_off, Lq, n_split=n_split, where="split form again")
     assert torch.equal(out, out2) and torch.equal(lse, lse2)
+
+
+def test_split_form_batch_and_heads():
+    """Key ranges with several batch rows, grouped heads and a seed list of its own per row (one
+    empty, one with entries past its count)."""
+    B, Hq, Hkv, L, Lq, q_off, ms = 3, 4, 2, 2100, 20, 1990, 12
+    a = synth.attn_inputs(synth.AttnConfig("custom", B, Hq, Hkv, L, 128, "bf16", 0, L, ms, "independent"), seed=31)
+    rng = np.random.default_rng(31)
+    si = np.sort(rng.choice(L, (B, ms), replace=False)).astype(np.int32)
+    si[2, :4] = [0, 1990, 2001, 2099]
+    counts = [0, ms, 4]
+    a["seed_idx"], a["n_seed"] = torch.from_numpy(si), torch.tensor(counts, dtype=torch.int32)
+    ignored = torch.from_numpy(np.where(np.arange(ms)[None] < np.array(counts)[:, None], si, -1).astype(np.int32))
+    q, kl, vl, kc, vc, sid, nsd = to_dev(a)
+    for n_split in (2, 4, 16):
+        announce(f"rect split form batch n_split={n_split}")
+        out, lse = cover.cover_attn_rect(q[:, :, q_off:q_off + Lq].contiguous(), kl, vl, kc, vc, q_off, sid, nsd,
+                                         n_split=n_split)
+        torch.cuda.synchronize()
+        rows = np.array([(b * Hq + h) * L + i for b in range(B) for h in range(Hq)
+                         for i in range(q_off, q_off + Lq)], np.int64)
+        ref_o, ref_l = oracle.attn(a["q"], a["k_live"], a["v_live"], a["k_cache"], a["v_cache"], ignored,
+                                   a["n_seed"], scale=a["scale"], mode="fast", rows=rows)
+        check_attn(out, lse, ref_o.reshape(B, Hq, Lq, 128), ref_l.reshape(B, Hq, Lq), torch.bfloat16, str(n_split))
 
 
 @pytest.mark.parametrize("B,Hq,L,Lq,n_split", [(1, 32, 2100, 64, 64), (2, 28, 1000, 100, 8), (4, 32, 700, 70, 3)])
