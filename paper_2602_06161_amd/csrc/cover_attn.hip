@@ -260,10 +260,11 @@ hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t stream) {
   // the chip is full of them, and one wave that walks all keys saves the merge and LDS (43 KB at
   // d = 64: three workgroups per CU): us with 8 waves and with 1, d64: 128 heads of L 256 62 / 40,
   // 2048 of L 65 197 / 72 (192 with a lane per query row), 32 of L 256 (512 tiles) 17 / 26; d128,
-  // 2048 heads of L 100 468 / 297.  Not at d = 128 past 640 keys (128 heads of L 1024 990 / 1058),
-  // where one wave's next tile arrives late.  Past 2^20 query tiles a workgroup takes several.
+  // 2048 heads of L 100 468 / 297.  Not at d = 128 past 384 keys (64 heads of L 520 174 / 203, of
+  // L 250 99 / 84), where one wave's next tile arrives late.  Past 2^20 query tiles a workgroup
+  // takes several.
   const int n_kt = (a.L + kFT - 1) / kFT;
-  const int nw = p.n_wg >= 2048 && (a.d == 64 || n_kt <= 40) ? 1 : (n_kt < kFWaves ? n_kt : kFWaves);
+  const int nw = p.n_wg >= 2048 && (a.d == 64 || n_kt <= 24) ? 1 : (n_kt < kFWaves ? n_kt : kFWaves);
   const dim3 block(64u * (unsigned)nw);
   const dim3 grid((unsigned)(p.n_wg < (1 << 20) ? p.n_wg : (1 << 20)));
   if (a.d == 128) {
